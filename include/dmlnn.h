@@ -164,9 +164,9 @@ DMLNN_API int conv2d_backward_data(dmlnn_dtype dtype, const void *W, const void 
  * mode 0 = dense (default), 1 = skip every MFMA step whose staged input
  * fragment is entirely zero (a wavefront ballot).  Where both modes run the
  * same kernel, results are bitwise equal up to the sign of zero results.  The
- * filter-resident forward has no skip form: with the skip on, that pass runs
- * the LDS-DMA kernel, whose summation order differs (equal within rounding);
- * conv2d_plan reports which kernel runs.  Process-wide setting; returns the
+ * filter-resident forward and the gather kernels have no skip form: with the
+ * skip on, those passes run a window kernel, whose summation order differs
+ * (equal within rounding); conv2d_plan reports which kernel runs.  Process-wide setting; returns the
  * previous mode, or -1 for an invalid mode. */
 DMLNN_API int dmlnn_set_zero_skip(int mode);
 
@@ -193,8 +193,11 @@ typedef enum {
     DMLNN_KERNEL_RESIDENT = 4,       /* filter-resident forward for small images (fp64)   */
     DMLNN_KERNEL_WGRAD_RING = 5,     /* backward_filter: row ring over the whole k range  */
     DMLNN_KERNEL_WGRAD_TILES = 6,    /* backward_filter: (filter tile, k range) blocks    */
-    DMLNN_KERNEL_WGRAD_POOL_SPARSE = 7 /* backward_filter from a pooled source with at most
-                                          32 filter columns: a sum over the pool windows  */
+    DMLNN_KERNEL_WGRAD_POOL_SPARSE = 7, /* backward_filter from a pooled source with at most
+                                           32 filter columns: a sum over the pool windows */
+    DMLNN_KERNEL_GATHER = 8,         /* matrix cores, patch rows gathered by LDS DMA, pixels
+                                        numbered over all images                          */
+    DMLNN_KERNEL_WGRAD_GATHER = 9    /* backward_filter with gathered patch rows          */
 } dmlnn_conv_kernel;
 
 typedef struct {
@@ -219,6 +222,8 @@ typedef struct {
      * bytes a lane; backward_filter: row stride of the staged gradient tile and
      * the slices a wide output row is cut into (0: tiles are whole rows). */
     int tile_stride, k_chunk, slice_stride, stage_bytes, window_bytes, slice_bytes, slice_vec;
+                       /* slice_vec of wgrad_gather: 1 the gradient, 2 also the patch rows move
+                          16 bytes a lane */
     int g_stride, row_slices;
     int pipelined;     /* register-staged kernels: 1 when a tile's global loads are held in
                           registers across the previous tile's MFMAs, 0 when staged directly */
@@ -229,7 +234,8 @@ typedef struct {
                           wave-uniform base plus the lane), bit 1 the gradient tile the
                           same way, bit 2 the new input row by LDS DMA into the one free
                           slot of an Hf + 1 slot ring (then window_rows = Hf + 1); 0
-                          where elements are dealt out to threads */
+                          where elements are dealt out to threads.  gather: the taps the
+                          kernel is specialised for (1, 9; 0: any) */
 } dmlnn_conv_plan;
 
 DMLNN_API int conv2d_plan(dmlnn_dtype dtype, int pass, int N, int C, int Hin, int Win, int F,

@@ -398,8 +398,10 @@ int conv2d_zero_skip_choice(dmlnn_dtype dtype, int pass, long long nnz, int N, i
     // the kernel the pass takes in the dense mode: when it has no skip form (the
     // vector-ALU small-M kernel, the filter-resident forward), the skip mode
     // would swap it for a different kernel, not skip its work
+    // (a pass that takes a gather kernel in the dense mode skips in its window kernel)
     dmlnn::ConvPlanInfo info;
-    if (dmlnn::conv_plan_info(dtype, pass, d, 0, 0, 0, 0, 0, 0, info) != hipSuccess) return -1;
+    if (dmlnn::conv_plan_info(dtype, pass, d, 0, dmlnn::kFormWindow, 0, 0, 0, 0, info) != hipSuccess)
+        return -1;
     if (info.kernel == dmlnn::kConvSmallM || info.kernel == dmlnn::kConvResident) return 0;
     // expected share of all-zero 64-value fragments under independent zeros
     const double density = (double)nnz / (double)n;

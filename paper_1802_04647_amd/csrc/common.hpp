@@ -177,6 +177,51 @@ __device__ __forceinline__ void dma_x4(i32x4 rsrc, void *lds_base, int voffset, 
     llvm_amdgcn_raw_buffer_load_lds(rsrc, (lds_void *)lds_base, 16, voffset, soffset, 0, 0);
 }
 
+// Element loads and stores through a buffer resource: an offset past the range
+// loads 0 and stores nothing.
+typedef int i32x2 __attribute__((ext_vector_type(2)));
+extern "C" __device__ int llvm_amdgcn_raw_buffer_load_i32(i32x4 rsrc, int voffset, int soffset,
+                                                          int aux)
+    __asm("llvm.amdgcn.raw.buffer.load.i32");
+extern "C" __device__ i32x2 llvm_amdgcn_raw_buffer_load_v2i32(i32x4 rsrc, int voffset, int soffset,
+                                                              int aux)
+    __asm("llvm.amdgcn.raw.buffer.load.v2i32");
+extern "C" __device__ void llvm_amdgcn_raw_buffer_store_i32(int v, i32x4 rsrc, int voffset,
+                                                            int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.store.i32");
+extern "C" __device__ void llvm_amdgcn_raw_buffer_store_v2i32(i32x2 v, i32x4 rsrc, int voffset,
+                                                              int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.store.v2i32");
+
+extern "C" __device__ i32x4 llvm_amdgcn_raw_buffer_load_v4i32(i32x4 rsrc, int voffset, int soffset,
+                                                              int aux)
+    __asm("llvm.amdgcn.raw.buffer.load.v4i32");
+extern "C" __device__ void llvm_amdgcn_raw_buffer_store_v4i32(i32x4 v, i32x4 rsrc, int voffset,
+                                                              int soffset, int aux)
+    __asm("llvm.amdgcn.raw.buffer.store.v4i32");
+
+template <typename T>
+__device__ __forceinline__ T buffer_load(i32x4 rsrc, int voffset, int soffset)
+{
+    if constexpr (sizeof(T) == 16)
+        return __builtin_bit_cast(T, llvm_amdgcn_raw_buffer_load_v4i32(rsrc, voffset, soffset, 0));
+    else if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, llvm_amdgcn_raw_buffer_load_v2i32(rsrc, voffset, soffset, 0));
+    else
+        return __builtin_bit_cast(T, llvm_amdgcn_raw_buffer_load_i32(rsrc, voffset, soffset, 0));
+}
+
+template <typename T>
+__device__ __forceinline__ void buffer_store(T v, i32x4 rsrc, int voffset, int soffset)
+{
+    if constexpr (sizeof(T) == 16)
+        llvm_amdgcn_raw_buffer_store_v4i32(__builtin_bit_cast(i32x4, v), rsrc, voffset, soffset, 0);
+    else if constexpr (sizeof(T) == 8)
+        llvm_amdgcn_raw_buffer_store_v2i32(__builtin_bit_cast(i32x2, v), rsrc, voffset, soffset, 0);
+    else
+        llvm_amdgcn_raw_buffer_store_i32(__builtin_bit_cast(int, v), rsrc, voffset, soffset, 0);
+}
+
 __device__ __forceinline__ void wait_dma() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // Kernels asking for more than 64 KiB of dynamic LDS must opt in (gfx950 has

@@ -1,0 +1,234 @@
+// Plans of the gather kernels (conv_gather.hpp): which sizes they take, and the
+// tile and split of a launch.  Host only.
+#include <cmath>
+
+#include "conv_gather.hpp"
+
+namespace dmlnn {
+namespace {
+
+constexpr int kCUs = 256;
+constexpr size_t kLdsCU = 160 * 1024;
+// Device rate of the matrix products, flop per microsecond and CU (a large
+// product reaches 72 and 154 TFLOP/s).
+double cu_rate(int tsz) { return tsz == 8 ? 0.28e6 : 0.6e6; }
+
+struct Tile {
+    int MW, NW;
+};
+constexpr Tile kTiles[] = {{1, 1}, {2, 1}, {3, 1}, {4, 1}, {5, 1}, {8, 1}, {2, 2}, {4, 2}, {8, 2}};
+
+// LDS bytes of a stage's patch rows, and of the stage (FwdLayout).
+int patch_bytes(int tsz, bool bwd, int form, Tile t)
+{
+    const int B = 64 * t.NW;
+    if (form == 9 && bwd) return 4 * (9 * B + 16) * tsz;
+    return gather::kRowBytes / tsz * (B + (tsz == 4 ? 4 : 8)) * tsz;
+}
+
+int stage_of(int tsz, bool bwd, int form, Tile t)
+{
+    const int A = 16 * t.MW, per = 256 / tsz, pad = (((16 - A) % per) + per) % per;
+    const int filter = form == 9 && bwd ? 4 * (A * 9 + pad) * tsz : A * gather::kRowBytes;
+    return filter + patch_bytes(tsz, bwd, form, t);
+}
+
+// Byte offsets are 32-bit, and a masked one (2^31 and up) plus the scalar offset
+// of a chunk's last channel must not wrap: tensors of up to 1 GiB.
+bool offsets_fit(size_t bytes, size_t plane_bytes)
+{
+    return bytes < 0x40000000ull && 64 * plane_bytes < 0x20000000ull;
+}
+
+}  // namespace
+
+GatherPlan gather_plan(int dtype, bool bwd, const ConvDims &d, bool mask)
+{
+    GatherPlan best = {};
+    const int tsz = dtype == 0 ? 8 : 4;
+    const int M = bwd ? d.C : d.F, Cs = bwd ? d.F : d.C;
+    const int Sh = bwd ? d.Hout : d.Hin, Sw = bwd ? d.Wout : d.Win;
+    const int Ho = bwd ? d.Hin : d.Hout, Wo = bwd ? d.Win : d.Wout;
+    const size_t plane = (size_t)Sh * Sw * tsz;
+    const int taps = d.Hf * d.Wf;
+    if (d.Hf > gather::kMaxTaps || d.Wf > gather::kMaxTaps || d.stride > 4) return best;
+    if (d.pad > 64 || !offsets_fit((size_t)d.N * Cs * plane + 64 * (size_t)(Sw + 1) * tsz, plane))
+        return best;
+    if ((size_t)(M + 128) * Cs * taps * tsz >= 0x40000000ull) return best;
+    if ((size_t)d.N * M * Ho * Wo * tsz >= 0x80000000ull) return best;
+    if ((long long)Ho * Wo >= (1 << 21) || (long long)d.N * Ho * Wo >= (1ll << 30)) return best;
+    const int form = bwd && d.stride > 1 ? 0 : (d.Hf == 3 && d.Wf == 3 ? 9 : (taps == 1 ? 1 : 0));
+    const int KC = bwd && form == 9 ? 36 : gather::kRowBytes / tsz;
+    gather::FwdArgs a = {};
+    a.N = d.N;
+    a.Ho = Ho;
+    a.Wo = Wo;
+    a.Hf = d.Hf;
+    a.Wf = d.Wf;
+    a.S = d.stride;
+    a.P = d.pad;
+    const int phases = bwd ? d.stride * d.stride : 1;
+    double best_us = 0.0;
+    for (const Tile t : kTiles) {
+        const int stage = stage_of(tsz, bwd, form, t), BM = 16 * t.MW, BN = 64 * t.NW;
+        const size_t lds = 2 * (size_t)stage + (mask ? patch_bytes(tsz, bwd, form, t) : 0);
+        if (lds > kLdsCU) continue;
+        // Microseconds: a chunk costs a CU its matrix time and the staging's
+        // (fitted to the tiles of 34 layers of all sizes, 10 to 500 us: the time
+        // of a tile is reproduced to 15-25%, the pick is 2% (forward) and 5%
+        // (backward) above the best tile's time); with few tiles the chain of a
+        // block's chunks, at 0.35 us each, bounds it instead.
+        // Short products end in the epilogue's stores: small blocks, more of them
+        // resident, overlap these better (K = 25, 204 rows: 31 against 42 us).
+        const double stage_us = 0.16 * t.NW + (bwd && form == 0 ? 0.055 : 0.015) * t.MW;
+        if (Cs * taps < 12 * KC && (t.NW > 1 || t.MW > 5)) continue;
+        double cost = 0.0, one = 0.0, chain = 0.0;
+        long long tiles = 0;
+        for (int ph = 0; ph < phases; ++ph) {
+            const gather::Geo g = bwd ? gather::geometry<true>(a, ph) : gather::geometry<false>(a, 0);
+            const long long n = ((long long)d.N * g.Hq * g.Wq + BN - 1) / BN * ((M + BM - 1) / BM);
+            const int chunks = (int)(((long long)Cs * g.Hfp * g.Wfp + KC - 1) / KC);
+            const double c = chunks * (2.0 * BM * BN * KC / cu_rate(tsz) + stage_us) + 0.5;
+            tiles += n;
+            cost += n * c;
+            one = std::max(one, c);
+            chain = std::max(chain, 0.35 * chunks);
+        }
+        if (tiles == 0 || tiles > 0x3fffffff) continue;
+        const double per_cu = (double)tiles / kCUs;
+        const int resident = (int)std::min<size_t>(4, kLdsCU / lds);
+        const double thr = cost / kCUs * std::ceil(per_cu) / per_cu;
+        const double lat = std::ceil(per_cu / resident) * chain;
+        const double us = std::pow(std::pow(thr, 4) + std::pow(lat, 4) + std::pow(one, 4), 0.25);
+        if (!best.MW || us < best_us) {
+            best_us = best.us = us;
+            best.MW = t.MW;
+            best.NW = t.NW;
+            best.blocks = (int)tiles;
+            best.stage = stage;
+        }
+    }
+    best.form = form;
+    return best;
+}
+
+GatherPlan gather_wgrad_plan(int dtype, const ConvDims &d, int max_splits)
+{
+    GatherPlan best = {};
+    const int tsz = dtype == 0 ? 8 : 4, taps = d.Hf * d.Wf, Q = d.Hout * d.Wout;
+    const size_t plane = (size_t)d.Hin * d.Win * tsz;
+    if (d.Hf > gather::kMaxTaps || d.Wf > gather::kMaxTaps || d.pad > 64) return best;
+    if (!offsets_fit((size_t)d.N * d.C * plane + 64 * (size_t)(d.Win + 1) * tsz,
+                     (size_t)(d.C + 16) * plane / 64) ||
+        (size_t)d.N * d.F * Q * tsz + 256 * (size_t)Q * tsz >= 0x40000000ull ||
+        (long long)d.N * Q >= (1ll << 30))
+        return best;
+    // a handful of chunks: nothing to pipeline (launch-bound either way)
+    if ((long long)d.N * Q < 256) return best;
+    const int E = 16 / tsz, KB = gather::kRowBytes / tsz;
+    const bool vec = Q % E == 0, xv = vec && taps == 1 && d.stride == 1 && d.pad == 0;
+    best.form = xv ? 2 : (vec ? 1 : 0);
+    const long long cols = xv ? d.C : (long long)(d.C + 1) / 2 * 2 * taps;
+    const long long chunks = ((long long)d.N * Q + KB - 1) / KB;
+    const double part = (double)d.F * d.C * taps * tsz;  // bytes of a split's partial
+    double best_us = 0.0;
+    for (const Tile t : kTiles) {
+        if (t.MW == 3) continue;
+        const int BM = 16 * t.MW, BN = 64 * t.NW, stage = (BM + BN) * gather::kRowBytes;
+        const long long tiles = (cols + BN - 1) / BN * ((d.F + BM - 1) / BM);
+        if (tiles > 0x3fffff) continue;
+        const double c = 2.0 * BM * BN * KB / cu_rate(tsz) +
+                         (xv ? 0.05 : 0.2) * t.NW + (vec ? 0.04 : 0.09) * t.MW + 0.1;
+        for (int r = 1; r <= 4; ++r) {
+            long long sp = std::max<long long>(1, (long long)kCUs * r / tiles);
+            sp = std::min(std::min<long long>(sp, max_splits), std::max<long long>(1, chunks / 4));
+            const long long per = (chunks + sp - 1) / sp;
+            const int resident = (int)std::min<size_t>(4, kLdsCU / (2 * (size_t)stage));
+            const double per_cu = (double)tiles * sp / kCUs;
+            const double thr = std::ceil(per_cu) * per * c, chain = 0.6 * per * std::ceil(per_cu / resident);
+            double us = std::pow(std::pow(thr, 4) + std::pow(chain, 4), 0.25);
+            if (sp > 1) us += 3.0 + 2.0 * sp * part / 3.0e6;
+            if (!best.MW || us < best_us) {
+                best_us = us;
+                best.MW = t.MW;
+                best.NW = t.NW;
+                best.splits = (int)sp;
+                best.blocks = (int)(tiles * sp);
+                best.stage = stage;
+            }
+        }
+    }
+    return best;
+}
+
+hipError_t launch_gather_f64(bool, const GatherPlan &, gather::FwdArgs, hipStream_t);
+hipError_t launch_gather_f32(bool, const GatherPlan &, gather::FwdArgs, hipStream_t);
+hipError_t launch_gather_wgrad_f64(const GatherPlan &, gather::WgArgs, hipStream_t);
+hipError_t launch_gather_wgrad_f32(const GatherPlan &, gather::WgArgs, hipStream_t);
+
+hipError_t launch_gather(int dtype, bool bwd, const GatherPlan &p, const void *src,
+                         const void *mask, const void *W, const void *bias, void *out, const ConvDims &d, int relu, hipStream_t s)
+{
+    const size_t tsz = dtype == 0 ? 8 : 4;
+    gather::FwdArgs a = {};
+    a.src = src;
+    a.mask = mask;
+    a.wgt = W;
+    a.bias = bias;
+    a.out = out;
+    a.N = d.N;
+    a.M = bwd ? d.C : d.F;
+    a.Cs = bwd ? d.F : d.C;
+    a.Sh = bwd ? d.Hout : d.Hin;
+    a.Sw = bwd ? d.Wout : d.Win;
+    a.Ho = bwd ? d.Hin : d.Hout;
+    a.Wo = bwd ? d.Win : d.Wout;
+    a.Hf = d.Hf;
+    a.Wf = d.Wf;
+    a.S = d.stride;
+    a.P = d.pad;
+    a.relu = relu;
+    a.m_tiles = (a.M + 16 * p.MW - 1) / (16 * p.MW);
+    a.src_bytes = (unsigned)((size_t)a.N * a.Cs * a.Sh * a.Sw * tsz);
+    a.w_bytes = (unsigned)((size_t)a.M * a.Cs * a.Hf * a.Wf * tsz);
+    return dtype == 0 ? launch_gather_f64(bwd, p, a, s) : launch_gather_f32(bwd, p, a, s);
+}
+
+hipError_t launch_gather_wgrad(int dtype, const GatherPlan &p, const void *X, const void *dout,
+                               const void *mask, void *dW, void *db, void *g_out, void *ws,
+                               const ConvDims &d, hipStream_t s)
+{
+    const size_t tsz = dtype == 0 ? 8 : 4;
+    const int taps = d.Hf * d.Wf, Q = d.Hout * d.Wout;
+    gather::WgArgs a = {};
+    a.X = X;
+    a.dout = dout;
+    a.mask = mask;
+    a.ws = ws;
+    a.dW = dW;
+    a.db = db;
+    a.g_out = g_out;
+    a.N = d.N;
+    a.C = d.C;
+    a.Hin = d.Hin;
+    a.Win = d.Win;
+    a.F = d.F;
+    a.Hf = d.Hf;
+    a.Wf = d.Wf;
+    a.S = d.stride;
+    a.P = d.pad;
+    a.Hout = d.Hout;
+    a.Wout = d.Wout;
+    const long long cols = p.form == 2 ? d.C : (long long)(d.C + 1) / 2 * 2 * taps;
+    a.nkr = (int)((cols + 64 * p.NW - 1) / (64 * p.NW));
+    a.nft = (d.F + 16 * p.MW - 1) / (16 * p.MW);
+    a.splits = p.splits;
+    a.want_db = db != nullptr;
+    a.x_bytes = (unsigned)((size_t)d.N * d.C * d.Hin * d.Win * tsz);
+    a.g_bytes = (unsigned)((size_t)d.N * d.F * Q * tsz);
+    const hipError_t e = dtype == 0 ? launch_gather_wgrad_f64(p, a, s) : launch_gather_wgrad_f32(p, a, s);
+    if (e != hipSuccess || p.splits == 1) return e;
+    return launch_wgrad_reduce(dtype, ws, dW, db, d.F * d.C * taps, d.F, p.splits, s);
+}
+
+}  // namespace dmlnn

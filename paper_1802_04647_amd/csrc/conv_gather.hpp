@@ -1,0 +1,820 @@
+// conv2d forward, backward_data and backward_filter as matrix products whose
+// patch operand is gathered straight from global memory into LDS (the gather
+// kernels).  Included by one source file per element type.
+//
+// The window kernels of conv_igemm.hip and conv_wgrad.hip stage the input rows
+// a pixel tile touches and address the taps inside them.  That needs vector
+// address arithmetic in the matrix loop, tiles inside one image and a window
+// that fits LDS.  Here a k-chunk of the patch matrix itself is staged, by LDS
+// DMA with an offset per lane, so
+//   - the matrix loop is LDS reads at constant offsets and MFMAs, nothing else
+//     (on gfx950 a vector instruction takes its issue cycles from the matrix
+//     pipe of its SIMD: the window kernel's loop ran 17% faster in fp32 and 7%
+//     in fp64 in a timing copy without its address arithmetic);
+//   - pixels are numbered over all images, so small images leave no tile
+//     partly empty;
+//   - backward_data of a strided layer runs one product per output phase
+//     (rows h with the same (h + pad) mod stride) over the filter taps that
+//     reach it, where the window kernels multiply the zeros of an up-sampled
+//     gradient (stride 2: four times the work).
+// Each input element is fetched once per tap that uses it, from L1 / L2; the
+// DMA moves 4 bytes a lane, about 28 bytes a clock per CU, of which a 64 x 128
+// tile needs 12 in either type.
+//
+// k order.  A chunk is 128 bytes of k per operand row (32 in fp32, 16 in
+// fp64).  A k-contiguous operand is stored [row][128 bytes], its 16-byte pieces
+// exchanged by the row (piece p of row r at p ^ (r & 7)), so that 16-byte reads
+// of 16 rows hit distinct banks; lane quarter q reads piece 4 g + q of group g
+// (g = 0, 1) and feeds its elements one by one to the MFMAs, so step s of the
+// group multiplies k = (4 g + q) E + s (E elements a piece).
+#pragma once
+
+#include <algorithm>
+#include <type_traits>
+
+#include "common.hpp"
+#include "internal.hpp"
+
+namespace dmlnn {
+namespace gather {
+
+constexpr int kThreads = 256;
+constexpr int kRowBytes = 128;  // bytes of k a chunk holds per operand row
+constexpr int kMaxTaps = 31;    // filter height and width a tap mask holds (bit 31: never valid)
+
+struct FwdArgs {
+    const void *src;   // [N][Cs][Sh][Sw]
+    const void *mask;  // backward, MASK: src counts where mask > 0
+    const void *wgt;   // forward: [M][Cs][Hf][Wf]; backward: [Cs][M][Hf][Wf]
+    const void *bias;  // or null: per row (bias_cols = 0) or per pixel (1, one image)
+    void *out;         // [N][M][Ho][Wo]
+    int N, M, Cs, Sh, Sw, Ho, Wo, Hf, Wf, S, P;
+    int relu, bias_cols, m_tiles;
+    unsigned src_bytes, w_bytes;
+};
+
+// Sub-problem of a launch: the pixels it computes, (h', w') in Hq x Wq of every
+// image, written at (oy0 + oS h', ox0 + oS w'), and the Hfp x Wfp taps it sums:
+// source cell (by0 + Sy h' + i, bx0 + Sy w' + j).  Forward: all pixels and taps.
+// Backward: phase (ry, rx) of the stride: the outputs with (h + P) mod S = ry;
+// tap i is filter row ry + S (Hfp - 1 - i).
+struct Geo {
+    int Hq, Wq, Hfp, Wfp, Sy, by0, bx0, oS, oy0, ox0;
+};
+
+__host__ __device__ inline void phase_axis(int r, int S, int P, int n, int nf, int &cnt, int &taps,
+                                           int &b0, int &o0)
+{
+    o0 = ((r - P) % S + S) % S;
+    cnt = o0 < n ? (n - o0 + S - 1) / S : 0;
+    taps = r < nf ? (nf - r + S - 1) / S : 0;
+    b0 = (o0 + P - r) / S - (taps - 1);
+}
+
+template <bool BWD>
+__host__ __device__ inline Geo geometry(const FwdArgs &a, int phase)
+{
+    Geo g;
+    if (!BWD) {
+        g = Geo{a.Ho, a.Wo, a.Hf, a.Wf, a.S, -a.P, -a.P, 1, 0, 0};
+    } else {
+        const int ry = phase / a.S, rx = phase - ry * a.S;
+        phase_axis(ry, a.S, a.P, a.Ho, a.Hf, g.Hq, g.Hfp, g.by0, g.oy0);
+        phase_axis(rx, a.S, a.P, a.Wo, a.Wf, g.Wq, g.Wfp, g.bx0, g.ox0);
+        if (g.Hfp == 0 || g.Wfp == 0) g.Hfp = g.Wfp = 0;  // no tap: the outputs are zero
+        g.Sy = 1;
+        g.oS = a.S;
+    }
+    return g;
+}
+
+// Bits [0, taps) that are set where tap t of a cell at coordinate c lands
+// outside [0, n); the bits above are set.
+__device__ __forceinline__ unsigned invalid_taps(int c, int n, int taps)
+{
+    const int lo = max(0, -c), hi = min(taps, n - c);
+    const int w = max(hi - lo, 0);
+    return w ? ~(((1u << w) - 1u) << lo) : ~0u;  // w <= 31, and lo < 31 when w > 0
+}
+
+__device__ __forceinline__ int mask_offset(int base, unsigned yinv, unsigned xinv, int sy, int sx)
+{
+    // bit 31 set (an offset past the buffer, which loads zeros) where the tap is invalid
+    return base | (int)(((yinv << sy) | (xinv << sx)) & 0x80000000u);
+}
+
+// T elements of a 16-byte piece
+template <typename T>
+struct Piece;
+template <>
+struct Piece<float> {
+    typedef f4 type;
+};
+template <>
+struct Piece<double> {
+    typedef double type __attribute__((ext_vector_type(2)));
+};
+
+// EL elements a lane stages at once
+template <typename T, int EL>
+struct Elems {
+    typedef T type;
+    static __device__ __forceinline__ T masked(T v, T m) { return m > T(0) ? v : T(0); }
+    static __device__ __forceinline__ T sum(T v) { return v; }
+};
+template <typename T>
+struct Elems<T, 16 / (int)sizeof(T)> {
+    typedef typename Piece<T>::type type;
+    static constexpr int EL = 16 / (int)sizeof(T);
+    static __device__ __forceinline__ type masked(type v, type m)
+    {
+#pragma unroll
+        for (int i = 0; i < EL; ++i) v[i] = m[i] > T(0) ? v[i] : T(0);
+        return v;
+    }
+    static __device__ __forceinline__ T sum(type v)
+    {
+        T s = v[0];
+#pragma unroll
+        for (int i = 1; i < EL; ++i) s += v[i];
+        return s;
+    }
+};
+
+template <typename T>
+constexpr int kE = 16 / (int)sizeof(T);           // elements of a piece
+template <typename T>
+constexpr int kKB = kRowBytes / (int)sizeof(T);   // k of a chunk
+// The form of a sub-problem: NT = 9 (3x3 taps), 1 (one tap) or 0 (any).
+//   A chunk is kKB k in the order (channel, tap), filter rows in exchanged
+//   pieces as above; the patch operand is stored [k][pixels], its row stride
+//   padded so that the four lane quarters of a read, E rows apart, are a quarter
+//   of the 256-byte bank period apart in fp32 and half of it in fp64.
+//   NT = 9 backward: a chunk is four channels, one a lane quarter, and a k-step
+//   one tap of each.  A wave stages the nine rows of one channel, and the
+//   channel's filter slab [row][9], contiguous in memory, in 16-byte pieces (the
+//   chunk's rows gathered 4 bytes a lane took 185 us where this takes 150: 64 x
+//   256 x 14x14, 256 channels, fp32).  Slabs and row groups are padded to
+//   quarters as above.  (Forward, where a filter row is k-contiguous, the same
+//   chunk measured slower than the pieces: 167 against 157 us.)
+template <typename T, int MW, int NW, bool BWD, int NT>
+struct FwdLayout {
+    static constexpr int tsz = sizeof(T), BM = 16 * MW, BN = 64 * NW;
+    static constexpr bool N9 = NT == 9 && BWD;
+    static constexpr int KC = N9 ? 36 : kKB<T>;        // k rows of a chunk
+    static constexpr int BNP = BN + (N9 ? 0 : (tsz == 4 ? 4 : 8));
+    static constexpr int BQ = 9 * BN + 16;             // N9: a channel's rows
+    static constexpr int PERIOD = tsz == 4 ? 64 : 32;  // elements of a bank period
+    static constexpr int SLAB = BM * 9 + ((16 - 16 * MW) % PERIOD + PERIOD) % PERIOD;
+    static constexpr int A_BYTES = N9 ? 4 * SLAB * tsz : BM * kRowBytes;
+    static constexpr int B_ELEMS = N9 ? 4 * BQ : KC * BNP;
+    static constexpr int STAGE = A_BYTES + B_ELEMS * tsz;
+    static constexpr int lds(bool mask) { return 2 * STAGE + (mask ? B_ELEMS * tsz : 0); }
+};
+
+// fp32 sums are kept in two levels: every kFlush chunks (256 k) the MFMA
+// accumulators are added to a second set and cleared, which shortens the chain
+// of roundings (K = 2304: error 6e-7 -> see below for what it measured).
+constexpr int kFlush = 8;
+
+// Forward and backward_data.  A block computes 16 MW rows x 64 NW pixels with
+// four waves side by side (16 NW pixels each).
+// NT: the taps of every sub-problem when they are 1 or 9 (1x1 and 3x3 filters
+// at stride 1, and every forward of such), else 0.  With NT a lane's masked
+// offsets are kept per tap, so a DMA instruction costs no vector instruction.
+// MASK (backward): the mask's patch rows go to a third LDS buffer and are folded
+// into the source's before their MFMAs (the sums are those of the masked source
+// bit for bit).
+template <typename T, int MW, int NW, bool BWD, int NT, bool MASK = false>
+__global__ __launch_bounds__(kThreads, 2) void conv_gather_kernel(FwdArgs a)
+{
+    using MF = Mfma<T>;
+    using LY = FwdLayout<T, MW, NW, BWD, NT>;
+    constexpr int tsz = sizeof(T), E = kE<T>, KB = LY::KC, BM = LY::BM, BN = LY::BN;
+    constexpr int BNP = LY::BNP, A_BYTES = LY::A_BYTES, STAGE = LY::STAGE;
+    constexpr bool N9 = LY::N9;
+    constexpr int NP = BN * tsz / 256;   // DMA instructions of a k row (64 or 32 pixels each)
+    constexpr int RW = KB / 4;           // k rows a wave stages
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int lane = lane_id(), wave = wave_id();
+    const int L = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int mt = L % a.m_tiles, m0 = mt * BM;
+    int pt = L / a.m_tiles;
+    Geo g = geometry<BWD>(a, 0);
+    int Pn = a.N * g.Hq * g.Wq;  // pixels of the sub-problem
+    if (BWD) {
+        for (int ph = 0; pt >= (Pn + BN - 1) / BN;) {
+            pt -= (Pn + BN - 1) / BN;
+            g = geometry<BWD>(a, ++ph);
+            Pn = a.N * g.Hq * g.Wq;
+        }
+    }
+    const int Qp = g.Hq * g.Wq, nt = g.Hfp * g.Wfp, K = a.Cs * nt;
+    const int plane = a.Sh * a.Sw;
+    const int p0 = pt * BN, n0 = p0 / Qp, r0 = p0 - n0 * Qp;
+    const float rcp_q = 1.0f / (float)Qp, rcp_w = 1.0f / (float)g.Wq;
+
+    // The buffer starts shY rows and shX cells before the tensor, so that the
+    // offset of a pixel's first tap is never negative; every lane that would
+    // read outside the tensor has its offset masked.
+    const int shY = max(0, -g.by0), shX = max(0, -g.bx0);
+    const unsigned shift = (unsigned)(shY * a.Sw + shX) * tsz;
+    const int range = (int)(a.src_bytes + shift);  // (the host keeps it below 2^31)
+    const i32x4 rs_src = buffer_rsrc(reinterpret_cast<const char *>(a.src) - shift, (unsigned)range);
+    const i32x4 rs_msk = MASK ? buffer_rsrc(reinterpret_cast<const char *>(a.mask) - shift, (unsigned)range)
+                              : rs_src;
+    const i32x4 rs_w = buffer_rsrc(a.wgt, a.w_bytes);
+    // a patch row's DMA, and its mask's to the same place of the third buffer
+    auto dma_row = [&](unsigned char *sb, int at, int voff, int so) {
+        dma_dword(rs_src, sb + at, voff, so);
+        if constexpr (MASK) dma_dword(rs_msk, smem + 2 * STAGE + at, voff, so);
+    };
+
+    // This lane's pixels of a k row: the byte offset of the first tap and the
+    // taps that fall outside the plane; with NT the masked offset of each tap.
+    constexpr int NM = NT ? NT : 1;
+    int base[NP][NM];
+    unsigned yinv[NP], xinv[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const int px = tsz == 4 ? i * 64 + lane : i * 32 + (lane >> 1);
+        const int v = r0 + px, dn = div_small(v, Qp, rcp_q), q = v - dn * Qp;
+        const int hy = div_small(q, g.Wq, rcp_w), wx = q - hy * g.Wq;
+        const int y = g.by0 + g.Sy * hy, x = g.bx0 + g.Sy * wx;
+        const bool in = p0 + px < Pn;
+        int b = in ? (((n0 + dn) * a.Cs * a.Sh + y + shY) * a.Sw + x + shX) * tsz : 0;
+        if (tsz == 8) b += 4 * (lane & 1);
+        yinv[i] = in ? invalid_taps(y, a.Sh, g.Hfp) : ~0u;
+        xinv[i] = in ? invalid_taps(x, a.Sw, g.Wfp) : ~0u;
+        if constexpr (NT != 0) {
+            constexpr int WT = NT == 9 ? 3 : 1;
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+                base[i][t] = mask_offset(b, yinv[i], xinv[i], 31 - t / WT, 31 - t % WT) < 0 ? kDmaZero : b;
+        } else {
+            base[i][0] = b;
+        }
+    }
+    // byte offset of tap t from the first (wave-uniform)
+    int tso[NM];
+#pragma unroll
+    for (int t = 0; t < NM; ++t) tso[t] = NT == 9 ? ((t / 3) * a.Sw + t % 3) * tsz : 0;
+
+    // Filter slice.  N9: wave w stages the slab of channel c0 + w, 16 bytes a
+    // lane.  Else forward: rows are k-contiguous, an instruction moves 8 rows, 16
+    // bytes a lane; backward: row c, k = (f, tap): 4 bytes a lane, two rows an
+    // instruction.  There the piece a lane fetches is the exchanged one of its slot.
+    constexpr int ROWS_I = BWD ? 2 : 8;
+    constexpr int PIECES = BM * 9 / E;  // N9: of a slab
+    constexpr int NA = N9 ? (PIECES + 63) / 64 : (BM / ROWS_I + 3) / 4;
+    int va = 0, af = 0, at = 0;
+    const int a_row = BWD ? (lane >> 5) : (lane >> 3);
+    if constexpr (N9) {
+        va = lane * 16;
+    } else if constexpr (!BWD) {
+        va = (a_row * K + ((lane & 7) ^ a_row) * E) * tsz;
+    } else {
+        const int d = lane & 31, piece = (d >> 2) ^ ((2 * wave + a_row) & 7);
+        const int kl = piece * E + (tsz == 4 ? (d & 3) : ((d & 3) >> 1));
+        af = nt ? kl / nt : 0;
+        at = kl - af * nt;
+    }
+    const unsigned m_wfp = BWD ? (65536u + max(g.Wfp, 1) - 1) / (unsigned)max(g.Wfp, 1) : 0;
+    // advance of (channel, tap) over a chunk
+    const int kb_c = nt ? KB / nt : 0, kb_t = KB - kb_c * nt;
+    const int kb_i = g.Wfp ? kb_t / g.Wfp : 0, kb_j = kb_t - kb_i * g.Wfp;
+    // (channel, tap row, tap column) of this wave's first k row
+    int kc = nt ? wave * RW / nt : 0;
+    int ki = g.Wfp ? (wave * RW - kc * nt) / g.Wfp : 0;
+    int kj = wave * RW - kc * nt - ki * g.Wfp;
+    int kt = wave * RW - kc * nt;  // the same as one tap index (NT = 9 forward)
+    const int wrap_j = (a.Sw - g.Wfp) * tsz, wrap_i = (plane - g.Hfp * a.Sw) * tsz;
+
+    auto issue = [&](int st, int k0) {
+        unsigned char *sa = smem + st * STAGE, *sb = sa + A_BYTES;
+        if constexpr (N9) {
+            // (lanes past the slab are inactive; a channel past the last lies past the buffer)
+            const int so = ((k0 / 9 + wave) * a.M + m0) * 9 * tsz;
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if (j * 64 + lane < PIECES)
+                    dma_x4(rs_w, sa + wave * LY::SLAB * tsz + j * 1024, va + j * 1024, so);
+        } else if constexpr (!BWD) {
+            // the lanes of the last chunk whose piece lies past K load zeros
+            int v = va;
+            if (k0 + KB > K && k0 + ((lane & 7) ^ a_row) * E >= K) v = kDmaZero;
+            const int so = ((m0 + wave * 8) * K + k0) * tsz;
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if (wave + 4 * j < BM / 8) dma_x4(rs_w, sa + (wave + 4 * j) * 1024, v, so + 32 * j * K * tsz);
+        } else {
+            // filter element (f, c, i, j) of k = (f, tap): tap (i'', j'') of the phase
+            const int i2 = (int)(__umul24(at, m_wfp) >> 16), j2 = at - i2 * g.Wfp;
+            const int ry = ((g.oy0 + a.P) % a.S), rx = ((g.ox0 + a.P) % a.S);
+            const int el = (ry + a.S * (g.Hfp - 1 - i2)) * a.Wf + rx + a.S * (g.Wfp - 1 - j2);
+            const int HfWf = a.Hf * a.Wf;
+            int v = ((af * a.M + a_row) * HfWf + el) * tsz;
+            if (tsz == 8) v += 4 * (lane & 1);
+            if (af >= a.Cs) v = kDmaZero;
+            const int so = (m0 + 2 * wave) * HfWf * tsz;
+#pragma unroll
+            for (int j = 0; j < NA; ++j)
+                if (wave + 4 * j < BM / 2) dma_dword(rs_w, sa + (wave + 4 * j) * 256, v, so + 8 * j * HfWf * tsz);
+            af += kb_c;
+            at += kb_t;
+            if (at >= nt) {
+                at -= nt;
+                ++af;
+            }
+        }
+        if constexpr (NT != 0) {
+            // Rows (c, t), (c, t + 1), ... from tap T0 of channel c0.  (Channels past
+            // the last: an offset past the buffer, 2^31 below a wrap for masked lanes.)
+            auto rows = [&](int c0, auto tc) {
+                constexpr int T0 = decltype(tc)::value;
+#pragma unroll
+                for (int r = 0; r < RW; ++r) {
+                    const int c = c0 + (T0 + r) / NM, t = (T0 + r) % NM;
+                    const int so = c < a.Cs ? c * plane * tsz + tso[t] : range;
+                    const int row = (N9 ? wave * LY::BQ + r * BN : (wave * RW + r) * BNP) * tsz;
+#pragma unroll
+                    for (int i = 0; i < NP; ++i) dma_row(sb, row + i * 256, base[i][t], so);
+                }
+            };
+            if constexpr (N9) {
+                rows(k0 / 9 + wave, std::integral_constant<int, 0>());
+            } else if constexpr (NT == 1) {
+                rows(k0 + wave * RW, std::integral_constant<int, 0>());
+            } else {
+                switch (kt) {  // one straight-line copy per starting tap
+                case 0: rows(kc, std::integral_constant<int, 0>()); break;
+                case 1: rows(kc, std::integral_constant<int, 1>()); break;
+                case 2: rows(kc, std::integral_constant<int, 2>()); break;
+                case 3: rows(kc, std::integral_constant<int, 3>()); break;
+                case 4: rows(kc, std::integral_constant<int, 4>()); break;
+                case 5: rows(kc, std::integral_constant<int, 5>()); break;
+                case 6: rows(kc, std::integral_constant<int, 6>()); break;
+                case 7: rows(kc, std::integral_constant<int, 7>()); break;
+                default: rows(kc, std::integral_constant<int, 8>()); break;
+                }
+                kt += kb_t;
+                kc += kb_c;
+                if (kt >= nt) {
+                    kt -= nt;
+                    ++kc;
+                }
+            }
+        } else {
+            int c = kc, ti = ki, tj = kj;
+            int so = (c * plane + ti * a.Sw + tj) * tsz;
+#pragma unroll
+            for (int r = 0; r < RW; ++r) {
+                const int sy = c < a.Cs ? 31 - ti : 0, sx = 31 - tj;
+                const int row = (wave * RW + r) * BNP * tsz;
+#pragma unroll
+                for (int i = 0; i < NP; ++i)
+                    dma_row(sb, row + i * 256, mask_offset(base[i][0], yinv[i], xinv[i], sy, sx), so);
+                so += tsz;
+                if (++tj == g.Wfp) {
+                    tj = 0;
+                    so += wrap_j;
+                    if (++ti == g.Hfp) {
+                        ti = 0;
+                        so += wrap_i;
+                        ++c;
+                    }
+                }
+            }
+            kj += kb_j;
+            ki += kb_i;
+            kc += kb_c;
+            if (kj >= g.Wfp) {
+                kj -= g.Wfp;
+                ++ki;
+            }
+            if (ki >= g.Hfp) {
+                ki -= g.Hfp;
+                ++kc;
+            }
+        }
+    };
+
+    typename MF::acc_t acc[MW][NW], sum[tsz == 4 ? MW : 1][tsz == 4 ? NW : 1];
+#pragma unroll
+    for (int x = 0; x < MW; ++x)
+#pragma unroll
+        for (int y = 0; y < NW; ++y) {
+            acc[x][y] = MF::zero();
+            if constexpr (tsz == 4) sum[x][y] = MF::zero();
+        }
+    int nflush = kFlush;
+    auto flush = [&]() {  // fp32: the accumulators to the second level
+        if constexpr (tsz == 4) {
+            nflush = kFlush;
+#pragma unroll
+            for (int x = 0; x < MW; ++x)
+#pragma unroll
+                for (int y = 0; y < NW; ++y) {
+                    sum[x][y] += acc[x][y];
+                    acc[x][y] = MF::zero();
+                }
+        }
+    };
+
+    const int li = lane & 15, q = lane >> 4;
+    typedef typename Piece<T>::type piece_t;
+    if (K > 0) {
+        issue(0, 0);
+        wait_dma();
+        __syncthreads();
+    }
+    int st = 0;
+    for (int k0 = 0; k0 < K; k0 += KB) {
+        if (!BWD && k0 + KB > K && K % E != 0) {
+            // the piece that straddles K holds the next row's first elements: zero them
+            T *sa = reinterpret_cast<T *>(smem + st * STAGE);
+            const int kt = K - k0;  // elements of the last chunk
+            for (int e = threadIdx.x; e < BM * E; e += kThreads) {
+                const int r = e / E, k = kt / E * E + e % E;
+                if (k >= kt) sa[r * KB + ((k / E) ^ (r & 7)) * E + k % E] = T(0);
+            }
+            __syncthreads();
+        }
+        if constexpr (MASK) {
+            const T *sm = reinterpret_cast<const T *>(smem + 2 * STAGE);
+            T *sw = reinterpret_cast<T *>(smem + st * STAGE + A_BYTES);
+            for (int e = threadIdx.x; e < LY::B_ELEMS; e += kThreads)
+                if (!(sm[e] > T(0))) sw[e] = T(0);
+            __syncthreads();  // the mask buffer is free for the next chunk's
+        }
+        if (k0 + KB < K) issue(st ^ 1, k0 + KB);
+        const unsigned char *sa = smem + st * STAGE;
+        if constexpr (N9) {
+            const T *sb = reinterpret_cast<const T *>(sa + A_BYTES) + q * LY::BQ + wave * 16 * NW + li;
+            const T *ar = reinterpret_cast<const T *>(sa) + q * LY::SLAB + li * 9;
+            T av[2][MW], bv[2][NW];
+            auto frag = [&](int t, T (&A)[MW], T (&B)[NW]) {
+#pragma unroll
+                // (backward: the taps of the correlation run against the filter's)
+                for (int x = 0; x < MW; ++x) A[x] = ar[x * 16 * 9 + 8 - t];
+#pragma unroll
+                for (int y = 0; y < NW; ++y) B[y] = sb[t * BN + y * 16];
+            };
+            frag(0, av[0], bv[0]);
+#pragma unroll
+            for (int t = 0; t < 9; ++t) {
+                if (t < 8) frag(t + 1, av[(t + 1) & 1], bv[(t + 1) & 1]);
+#pragma unroll
+                for (int y = 0; y < NW; ++y)
+#pragma unroll
+                    for (int x = 0; x < MW; ++x) acc[x][y] = MF::mma(av[t & 1][x], bv[t & 1][y], acc[x][y]);
+            }
+        } else {
+        const T *sb = reinterpret_cast<const T *>(sa + A_BYTES) + q * E * BNP + wave * 16 * NW + li;
+        const unsigned char *ar = sa + li * kRowBytes;
+#pragma unroll
+        for (int gq = 0; gq < 2; ++gq) {
+            piece_t av[MW];
+#pragma unroll
+            for (int x = 0; x < MW; ++x)
+                av[x] = *reinterpret_cast<const piece_t *>(ar + x * 16 * kRowBytes +
+                                                           (((4 * gq + q) ^ (li & 7)) * 16));
+#pragma unroll
+            for (int s = 0; s < E; ++s) {
+                T bv[NW];
+#pragma unroll
+                for (int y = 0; y < NW; ++y) bv[y] = sb[(gq * 4 * E + s) * BNP + y * 16];
+#pragma unroll
+                for (int y = 0; y < NW; ++y)
+#pragma unroll
+                    for (int x = 0; x < MW; ++x) acc[x][y] = MF::mma(av[x][s], bv[y], acc[x][y]);
+            }
+        }
+        }
+        if (tsz == 4 && --nflush == 0) flush();
+        wait_dma();
+        __syncthreads();
+        st ^= 1;
+    }
+    if constexpr (tsz == 4) {
+        flush();
+#pragma unroll
+        for (int x = 0; x < MW; ++x)
+#pragma unroll
+            for (int y = 0; y < NW; ++y) acc[x][y] = sum[x][y];
+    }
+
+    const T *bias = reinterpret_cast<const T *>(a.bias);
+    T bm[MW][4];
+#pragma unroll
+    for (int x = 0; x < MW; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + 16 * x + MF::row(lane, r);
+            bm[x][r] = (!BWD && bias && !a.bias_cols && m < a.M) ? bias[m] : T(0);
+        }
+    const size_t plane_o = (size_t)a.Ho * a.Wo;
+#pragma unroll
+    for (int y = 0; y < NW; ++y) {
+        const int px = wave * 16 * NW + y * 16 + li;
+        if (p0 + px >= Pn) continue;
+        const int v = r0 + px, dn = div_small(v, Qp, rcp_q), qq = v - dn * Qp;
+        const int hy = div_small(qq, g.Wq, rcp_w), wx = qq - hy * g.Wq;
+        const size_t o = (size_t)(n0 + dn) * a.M * plane_o +
+                         (size_t)(g.oy0 + g.oS * hy) * a.Wo + g.ox0 + g.oS * wx;
+        const T bc = (!BWD && bias && a.bias_cols) ? bias[qq] : T(0);
+        T *out = reinterpret_cast<T *>(a.out) + o;
+#pragma unroll
+        for (int x = 0; x < MW; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int m = m0 + 16 * x + MF::row(lane, r);
+                if (m >= a.M) continue;
+                T val = acc[x][y][r];
+                if (!BWD) val = relu_if(val + bm[x][r] + bc, a.relu);
+                out[(size_t)m * plane_o] = val;
+            }
+    }
+}
+
+// ------------------------------------------------------------ backward_filter
+struct WgArgs {
+    const void *X, *dout, *mask;  // mask (out_fwd) or null
+    void *ws;                     // [splits][F][K] partials, then [splits][F] bias partials
+    void *dW, *db;                // written instead of the partials when splits = 1
+    void *g_out;                  // or null
+    int N, C, Hin, Win, F, Hf, Wf, S, P, Hout, Wout;
+    int nkr, nft, splits, want_db;
+    unsigned x_bytes, g_bytes;
+};
+
+template <typename T>
+constexpr int wg_stage_bytes(int MW, int NW)
+{
+    return (16 * MW + 64 * NW) * kRowBytes;
+}
+
+// dW[f, k] = sum over pixels p of g[f, p] x[k, p], split over blocks along p.
+// A block computes 16 MW filters x 64 NW columns over its pixel range, walking
+// chunks of 128 bytes of pixels.  Both operands are stored [row][pixels].  The
+// gradient goes through registers, where the relu mask is applied; the patch
+// rows are gathered by LDS DMA, two columns an instruction: channels 2 c and
+// 2 c + 1 of one tap, so that the tap is the same for all lanes (column 2 u + h
+// of a block is pair u, channel 2 c + h).
+// VEC: Q is a multiple of the piece (no piece crosses an image): gradient, mask
+// and the emitted gradient move 16 bytes a lane.  XV: also a 1x1 filter at
+// stride 1 without padding, whose patch rows are the planes: they too move 16
+// bytes a lane, eight columns an instruction.
+template <typename T, int MW, int NW, bool VEC, bool XV>
+__global__ __launch_bounds__(kThreads, 2) void wgrad_gather_kernel(WgArgs a)
+{
+    using MF = Mfma<T>;
+    constexpr int tsz = sizeof(T), E = kE<T>, KB = kKB<T>, BM = 16 * MW, BN = 64 * NW;
+    constexpr int A_BYTES = BM * kRowBytes, STAGE = wg_stage_bytes<T>(MW, NW);
+    constexpr int EL = VEC ? E : 1;      // gradient elements a lane moves
+    constexpr int LR = KB / EL;          // lanes of a gradient row
+    constexpr int RP = kThreads / LR;    // gradient rows a pass of the block stages
+    constexpr int NJ = (BM + RP - 1) / RP;
+    constexpr int NI = BN / 8;           // patch DMA instructions of a wave (2 columns each)
+    typedef typename Elems<T, EL>::type el_t;
+    extern __shared__ __align__(16) unsigned char smem[];
+
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const int L = xcd_logical_block(blockIdx.x, gridDim.x);
+    const int kr = L % a.nkr, rest = L / a.nkr;
+    const int ft = rest % a.nft, split = rest / a.nft;
+    const int f0 = ft * BM, u0 = kr * (BN / 2);
+    const int Q = a.Hout * a.Wout, nt = a.Hf * a.Wf, plane = a.Hin * a.Win;
+    const int Pn = a.N * Q, nchunk = (Pn + KB - 1) / KB;
+    const int cb = (int)((long long)split * nchunk / a.splits);
+    const int ce = (int)((long long)(split + 1) * nchunk / a.splits);
+
+    // Gradient: thread (row tid / KB, pixel tid % KB) of each pass.
+    const i32x4 rs_g = buffer_rsrc(a.dout, a.g_bytes);
+    const i32x4 rs_m = buffer_rsrc(a.mask ? a.mask : a.dout, a.g_bytes);
+    const i32x4 rs_o = buffer_rsrc(a.g_out ? a.g_out : a.dout, a.g_bytes);
+    const bool emit = a.g_out != nullptr && kr == 0, sum_db = a.want_db && kr == 0;
+    const int gl = tid % LR * EL, gr = tid / LR;
+    int gp = cb * KB + gl;                         // pixel
+    int gn = gp / Q, gq = gp - gn * Q;             // image, cell
+    const int kb_n = KB / Q, kb_q = KB - kb_n * Q;
+    const int g_lds = gr * kRowBytes + (((gl / E) ^ (gr & 7)) * 16) + (gl % E) * tsz;
+    el_t gv[NJ], gm[NJ];
+    int g_off = 0;  // of the loaded chunk
+    T dbacc[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) dbacc[j] = T(0);
+
+    auto load_g = [&]() {
+        g_off = gp < Pn ? ((gn * a.F + f0 + gr) * Q + gq) * tsz : kDmaZero;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) gv[j] = buffer_load<el_t>(rs_g, g_off, j * RP * Q * tsz);
+        if (a.mask) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) gm[j] = buffer_load<el_t>(rs_m, g_off, j * RP * Q * tsz);
+        }
+        gp += KB;
+        gn += kb_n;
+        gq += kb_q;
+        if (gq >= Q) {
+            gq -= Q;
+            ++gn;
+        }
+    };
+    auto store_g = [&](int st) {
+        unsigned char *sa = smem + st * STAGE + g_lds;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            if (a.mask) gv[j] = Elems<T, EL>::masked(gv[j], gm[j]);
+            if (BM % RP == 0 || gr + j * RP < BM)
+                *reinterpret_cast<el_t *>(sa + j * RP * kRowBytes) = gv[j];
+            if (sum_db) dbacc[j] += Elems<T, EL>::sum(gv[j]);
+        }
+    };
+    auto emit_g = [&]() {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const int r = gr + j * RP;
+            if (r < BM && f0 + r < a.F) buffer_store<el_t>(gv[j], rs_o, g_off, j * RP * Q * tsz);
+        }
+    };
+
+    // Patch rows: instruction ii (wave ii % 4) holds pair u0 + ii; lane half r2 the
+    // channel, the rest of the lane the pixel of the slot's exchanged piece.
+    // XV: 8 columns an instruction, in columns' own order (no pairs).
+    const int r2 = XV ? lane >> 3 : lane >> 5, d5 = lane & 31;
+    const int pl = XV ? ((lane & 7) ^ r2) * E : ((d5 >> 2) ^ ((2 * wave + r2) & 7)) * E + (tsz == 4 ? (d5 & 3) : ((d5 & 3) >> 1));
+    const unsigned shift = (unsigned)(a.P * a.Win + a.P) * tsz;
+    const i32x4 rs_x = buffer_rsrc(reinterpret_cast<const char *>(a.X) - shift,
+                                   min(a.x_bytes + shift, 0x7fffffffu));
+    int xp = cb * KB + pl;
+    int xn = xp / Q, xh = (xp - xn * Q) / a.Wout, xw = xp - xn * Q - xh * a.Wout;
+    int xoff = ((xn * a.C + r2) * plane + xh * a.S * a.Win + xw * a.S) * tsz;
+    if (tsz == 8 && !XV) xoff += 4 * (lane & 1);
+    const int kb_h = kb_q / a.Wout, kb_w = kb_q - kb_h * a.Wout;
+    const int adv0 = (kb_n * a.C * plane + kb_h * a.S * a.Win + kb_w * a.S) * tsz;
+    const int adv_w = (a.S * a.Win - a.Wout * a.S) * tsz;
+    const int adv_h = (a.C * plane - a.Hout * a.S * a.Win) * tsz;
+    // pair u = t * npc + c2: (tap, channel pair) of this wave's first instruction
+    const int npc = (a.C + 1) / 2;
+    const int ut = (u0 + wave) / npc, uc = u0 + wave - ut * npc;
+    const int ut_i = ut / a.Wf;
+    auto issue_x = [&](int st) {
+        unsigned char *sb = smem + st * STAGE + A_BYTES + wave * (XV ? 1024 : 256);
+        const bool in = xp < Pn;
+        if constexpr (XV) {
+            const int v = in ? xoff : kDmaZero;
+            const int so = (2 * u0 + wave * 8) * plane * tsz;
+#pragma unroll
+            for (int j = 0; j < BN / 32; ++j)
+                dma_x4(rs_x, sb + j * 4096, v, so + j * 32 * plane * tsz);
+        } else {
+        const unsigned yinv = in ? invalid_taps(xh * a.S - a.P, a.Hin, a.Hf) : ~0u;
+        const unsigned xinv = in ? invalid_taps(xw * a.S - a.P, a.Win, a.Wf) : ~0u;
+        int t = ut, c2 = uc;
+        int ti = ut_i, tj = ut - ut_i * a.Wf;
+        int v = mask_offset(xoff, yinv, xinv, t < nt ? 31 - ti : 0, 31 - tj);
+        int so = (2 * c2 * plane + ti * a.Win + tj) * tsz;
+#pragma unroll
+        for (int j = 0; j < NI; ++j) {
+            dma_dword(rs_x, sb + j * 1024, v, so);
+            c2 += 4;
+            so += 8 * plane * tsz;
+            if (c2 >= npc) {  // the next tap (npc >= 4) or one further on
+                do {
+                    c2 -= npc;
+                    ++t;
+                    if (++tj == a.Wf) {
+                        tj = 0;
+                        ++ti;
+                    }
+                } while (c2 >= npc);
+                v = mask_offset(xoff, yinv, xinv, t < nt ? 31 - ti : 0, 31 - tj);
+                so = t < nt ? (2 * c2 * plane + ti * a.Win + tj) * tsz : 0;
+            }
+        }
+        }
+        xp += KB;
+        xw += kb_w;
+        xh += kb_h;
+        xoff += adv0;
+        if (xw >= a.Wout) {
+            xw -= a.Wout;
+            ++xh;
+            xoff += adv_w;
+        }
+        if (xh >= a.Hout) {
+            xh -= a.Hout;
+            xoff += adv_h;
+        }
+    };
+
+    typename MF::acc_t acc[MW][NW], sum[tsz == 4 ? MW : 1][tsz == 4 ? NW : 1];
+#pragma unroll
+    for (int x = 0; x < MW; ++x)
+#pragma unroll
+        for (int y = 0; y < NW; ++y) {
+            acc[x][y] = MF::zero();
+            if constexpr (tsz == 4) sum[x][y] = MF::zero();
+        }
+    int nflush = kFlush;
+    auto flush = [&]() {  // fp32: the accumulators to the second level
+        if constexpr (tsz == 4) {
+            nflush = kFlush;
+#pragma unroll
+            for (int x = 0; x < MW; ++x)
+#pragma unroll
+                for (int y = 0; y < NW; ++y) {
+                    sum[x][y] += acc[x][y];
+                    acc[x][y] = MF::zero();
+                }
+        }
+    };
+
+    const int li = lane & 15, q = lane >> 4;
+    typedef typename Piece<T>::type piece_t;
+    if (cb < ce) {
+        load_g();
+        issue_x(0);
+        store_g(0);
+        wait_dma();
+        __syncthreads();
+        if (emit) emit_g();
+    }
+    int st = 0;
+    for (int ch = cb; ch < ce; ++ch) {
+        const bool more = ch + 1 < ce;
+        if (more) {
+            load_g();
+            issue_x(st ^ 1);
+        }
+        const unsigned char *sa = smem + st * STAGE;
+        const unsigned char *ar = sa + li * kRowBytes;
+        const unsigned char *br = sa + A_BYTES + (wave * 16 * NW + li) * kRowBytes;
+#pragma unroll
+        for (int gq2 = 0; gq2 < 2; ++gq2) {
+            const int po = ((4 * gq2 + q) ^ (li & 7)) * 16;
+            piece_t av[MW], bv[NW];
+#pragma unroll
+            for (int x = 0; x < MW; ++x)
+                av[x] = *reinterpret_cast<const piece_t *>(ar + x * 16 * kRowBytes + po);
+#pragma unroll
+            for (int y = 0; y < NW; ++y)
+                bv[y] = *reinterpret_cast<const piece_t *>(br + y * 16 * kRowBytes + po);
+#pragma unroll
+            for (int s = 0; s < E; ++s)
+#pragma unroll
+                for (int y = 0; y < NW; ++y)
+#pragma unroll
+                    for (int x = 0; x < MW; ++x) acc[x][y] = MF::mma(av[x][s], bv[y][s], acc[x][y]);
+        }
+        if (more) store_g(st ^ 1);
+        if (tsz == 4 && --nflush == 0) flush();
+        wait_dma();
+        __syncthreads();
+        if (more && emit) emit_g();
+        st ^= 1;
+    }
+    if constexpr (tsz == 4) {
+        flush();
+#pragma unroll
+        for (int x = 0; x < MW; ++x)
+#pragma unroll
+            for (int y = 0; y < NW; ++y) acc[x][y] = sum[x][y];
+    }
+
+    const int K = a.C * nt;
+    T *wsp = a.splits == 1 ? reinterpret_cast<T *>(a.dW)
+                           : reinterpret_cast<T *>(a.ws) + (size_t)split * a.F * K;
+#pragma unroll
+    for (int y = 0; y < NW; ++y) {
+        const int col = wave * 16 * NW + y * 16 + li;
+        const int u = u0 + (col >> 1), t = XV ? 0 : u / npc, c = 2 * (u - t * npc) + (col & 1);
+        if (c >= a.C || t >= nt) continue;
+#pragma unroll
+        for (int x = 0; x < MW; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int f = f0 + 16 * x + MF::row(lane, r);
+                if (f < a.F) wsp[(size_t)f * K + c * nt + t] = acc[x][y][r];
+            }
+    }
+    if (sum_db) {
+        // a row is LR consecutive lanes: a fixed butterfly over them
+        T *wdb = a.splits == 1 ? reinterpret_cast<T *>(a.db)
+                               : reinterpret_cast<T *>(a.ws) + (size_t)a.splits * a.F * K +
+                                     (size_t)split * a.F;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            T v = dbacc[j];
+#pragma unroll
+            for (int off = LR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
+            const int r = gr + j * RP;
+            if (gl == 0 && r < BM && f0 + r < a.F) wdb[f0 + r] = v;
+        }
+    }
+}
+
+}  // namespace gather
+}  // namespace dmlnn

@@ -1,0 +1,71 @@
+// Kernel choice of the gather kernels for one element type.
+#pragma once
+
+#include "conv_gather.hpp"
+
+namespace dmlnn {
+namespace gather {
+
+// One entry per tile of the plans.
+#define DMLNN_GATHER_TILES(X) X(1, 1) X(2, 1) X(3, 1) X(4, 1) X(5, 1) X(8, 1) X(2, 2) X(4, 2) X(8, 2)
+
+template <typename K, typename A>
+hipError_t start(K k, int blocks, size_t lds, const A &a, hipStream_t s)
+{
+    const hipError_t e = allow_dynamic_lds(k, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(kThreads), lds, s, a);
+    return hipGetLastError();
+}
+
+template <typename T, bool BWD, int MW, int NW, int NT>
+hipError_t launch_form(const GatherPlan &p, const FwdArgs &a, hipStream_t s)
+{
+    using L = FwdLayout<T, MW, NW, BWD, NT>;
+    if (p.stage != L::STAGE) return hipErrorInvalidValue;
+    if constexpr (BWD && L::lds(true) <= 160 * 1024)
+        if (a.mask)
+            return start(conv_gather_kernel<T, MW, NW, BWD, NT, true>, p.blocks, L::lds(true), a, s);
+    if (a.mask) return hipErrorInvalidValue;
+    if constexpr (L::lds(false) <= 160 * 1024)
+        return start(conv_gather_kernel<T, MW, NW, BWD, NT>, p.blocks, L::lds(false), a, s);
+    return hipErrorInvalidValue;
+}
+
+template <typename T, bool BWD, int MW, int NW>
+hipError_t launch_tile(const GatherPlan &p, const FwdArgs &a, hipStream_t s)
+{
+    if (p.form == 9) return launch_form<T, BWD, MW, NW, 9>(p, a, s);
+    if (p.form == 1) return launch_form<T, BWD, MW, NW, 1>(p, a, s);
+    return launch_form<T, BWD, MW, NW, 0>(p, a, s);
+}
+
+template <typename T, bool BWD>
+hipError_t launch(const GatherPlan &p, const FwdArgs &a, hipStream_t s)
+{
+#define X(mw, nw) \
+    if (p.MW == mw && p.NW == nw) return launch_tile<T, BWD, mw, nw>(p, a, s);
+    DMLNN_GATHER_TILES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+template <typename T>
+hipError_t launch_wgrad(const GatherPlan &p, const WgArgs &a, hipStream_t s)
+{
+#define X(mw, nw)                                                                             \
+    if (p.MW == mw && p.NW == nw) {                                                           \
+        if (p.stage != wg_stage_bytes<T>(mw, nw)) return hipErrorInvalidValue;                \
+        if (p.form == 2)                                                                      \
+            return start(wgrad_gather_kernel<T, mw, nw, true, true>, p.blocks, 2 * (size_t)p.stage, a, s); \
+        if (p.form == 1)                                                                      \
+            return start(wgrad_gather_kernel<T, mw, nw, true, false>, p.blocks, 2 * (size_t)p.stage, a, s); \
+        return start(wgrad_gather_kernel<T, mw, nw, false, false>, p.blocks, 2 * (size_t)p.stage, a, s);  \
+    }
+    DMLNN_GATHER_TILES(X)
+#undef X
+    return hipErrorInvalidValue;
+}
+
+}  // namespace gather
+}  // namespace dmlnn

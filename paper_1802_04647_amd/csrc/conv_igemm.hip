@@ -70,6 +70,7 @@ struct IgemmArgs {
     int bank_off[kMaxBanks + 1];
     void *bank_out[kMaxBanks];
     int require_dma;  // 1: return hipErrorNotSupported instead of using the register path
+    int taps9;        // LDS-DMA kernel with NB = 7: 1 for its 3x3 loop
     int k4;           // LDS-DMA kernel with NB = 1: 0, or the row blocks (2 or 4) of the
                       // four-way k split
     // Sparse input (forward, register-staged kernel): X given in CSR; csr_row
@@ -380,8 +381,9 @@ struct DmaLayout {
                 // filter, and no pair mixes a tap with a zero column)
 };
 
+// T9: the 3x3 loop over groups of four channels (below).
 template <typename T, int NB, bool BWD, bool ZSKIP, bool KS, bool POOL, int K4 = 0,
-          bool PB = false>
+          bool PB = false, bool T9 = false>
 __global__ __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_eu(2, sizeof(T) == 4 ? 3 : 2))) void conv_igemm_dma_kernel(IgemmArgs a, DmaLayout L,
                                                                      unsigned w_bytes)
 {
@@ -522,31 +524,42 @@ __global__ __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_eu(2, 
         return reinterpret_cast<T *>(stages + st * L.stage_bytes + L.src_bytes);
     };
     T *const s_msk = reinterpret_cast<T *>(stages + 2 * L.stage_bytes);
+    // DMA instructions of this wave (w, w + 4, ...).  Issued up to a count, not
+    // each under its own test: forty tests a chunk held their conditions in
+    // spilled scalars, and took 4-5% of the benchmark layer's passes (forward
+    // fp64 1015 -> 970 us, fp32 547 -> 527).
+    const int nis_w = (NIs - wave + 3) >> 2, nia_w = (NIa - wave + 3) >> 2;
     auto issue = [&](int st, int c0) {
         unsigned char *ps = reinterpret_cast<unsigned char *>(stage_src(st));
         unsigned char *pm = reinterpret_cast<unsigned char *>(s_msk);
         unsigned char *pa = reinterpret_cast<unsigned char *>(stage_a(st));
         const int so_src = (int)((size_t)c0 * a.Sh * a.Sw * sizeof(T));
         const int so_w = (int)((size_t)c0 * (BWD ? a.M : 1) * a.HfWf * sizeof(T));
+        if (!PB && !has_mask) {
 #pragma unroll
-        for (int j = 0; j < kMaxDmaS; ++j) {
-            const int ii = wave + 4 * j;
-            if (!PB && ii < NIs) {
-                dma_dword(rs_src, ps + ii * 256, vs_off[j], so_src);
-                if (has_mask) dma_dword(rs_msk, pm + ii * 256, vs_off[j], so_src);
+            for (int j = 0; j < kMaxDmaS; ++j) {
+                if (j >= nis_w) break;
+                dma_dword(rs_src, ps + (wave + 4 * j) * 256, vs_off[j], so_src);
+            }
+        } else if (!PB) {
+#pragma unroll
+            for (int j = 0; j < kMaxDmaS; ++j) {
+                if (j >= nis_w) break;
+                dma_dword(rs_src, ps + (wave + 4 * j) * 256, vs_off[j], so_src);
+                dma_dword(rs_msk, pm + (wave + 4 * j) * 256, vs_off[j], so_src);
             }
         }
         if (avec) {
 #pragma unroll
             for (int j = 0; j < kMaxDmaA; ++j) {
-                const int ii = wave + 4 * j;
-                if (ii < NIa) dma_x4(rs_w, pa + ii * 1024, va_off[j], so_w);
+                if (j >= nia_w) break;
+                dma_x4(rs_w, pa + (wave + 4 * j) * 1024, va_off[j], so_w);
             }
         } else {
 #pragma unroll
             for (int j = 0; j < kMaxDmaA; ++j) {
-                const int ii = wave + 4 * j;
-                if (ii < NIa) dma_dword(rs_w, pa + ii * 256, va_off[j], so_w);
+                if (j >= nia_w) break;
+                dma_dword(rs_w, pa + (wave + 4 * j) * 256, va_off[j], so_w);
             }
         }
     };
@@ -687,7 +700,50 @@ __global__ __launch_bounds__(kThreads, 2) __attribute__((amdgpu_waves_per_eu(2, 
                 acc[1][y] = MF::mma(fa1, bv, acc[1][y]);
             }
         };
-        if (!K4) {
+        if constexpr (T9) {
+            // 3x3 filters, chunks of whole groups of four channels: lane quarter q
+            // takes channel 4 g + q and a k-step is one tap of the four, so within a
+            // window row every LDS address is a lane base plus a constant.  (A
+            // vector instruction takes its issue cycles from the matrix pipe: with
+            // the tap arithmetic of the general loop, about twenty a step, the
+            // layer's matrix loop ran at 89% of the MFMA rate in fp64 and 80% in
+            // fp32: forward 970 -> 943 us and 527 -> 498, backward_data 990 -> 960 and
+            // 521 -> 476.)  The barrier after each step keeps a later step's reads
+            // from being hoisted into registers that are not there.
+            const int q = lane >> 4;
+            for (int g = 0; g < a.KC; g += 4) {
+                const T *ar0 = stage_a(st) + (mrow + (lane & 15)) * a.SA + (g + q) * 9;
+                const T *ar1 = ar0 + 16 * a.SA;
+                const T *bp = s_src + (g + q) * CHn;
+                int bo[NB];
+#pragma unroll
+                for (int y = 0; y < NB; ++y) bo[y] = lbase[y];
+                T fa[2][2], fb[2][NB];
+                auto tap = [&](int t, T (&A)[2], T (&B)[NB]) {
+                    A[0] = ar0[t];
+                    A[1] = ar1[t];
+#pragma unroll
+                    for (int y = 0; y < NB; ++y) {
+                        if (t == 3 || t == 6) bo[y] += a.Wpad;
+                        B[y] = bp[bo[y] + t % 3];
+                    }
+                };
+                tap(0, fa[0], fb[0]);
+#pragma unroll
+                for (int t = 0; t < 9; ++t) {
+                    if (t < 8) tap(t + 1, fa[(t + 1) & 1], fb[(t + 1) & 1]);
+                    mma_step(fa[t & 1][0], fa[t & 1][1], fb[t & 1]);
+                    if (!ZSKIP) {
+#pragma unroll
+                        for (int y = 0; y < NB + 2; ++y) {  // a read, an MFMA, ...
+                            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        } else if constexpr (!K4) {
             // With ksplit, wave half wm takes the steps kk = 4*wm, 4*wm + 8, ...
             const int kstep = KS ? 8 : 4;
             int kk = KS ? 4 * wm : 0;
@@ -1466,20 +1522,22 @@ hipError_t launch_dma_ks(const IgemmArgs &a, const Plan &p, const DmaLayout &L, 
 {
     dim3 grid(nimg * p.tiles_per_img, p.m_tiles), block(kThreads);
     hipError_t e;
-    if (PB) {  // the pooled source has no zero-skip form
-        auto k = conv_igemm_dma_kernel<T, NB, BWD, false, KS, POOL, K4, true>;
+    auto start = [&](auto k) {
         if ((e = allow_dynamic_lds(k, p.lds)) != hipSuccess) return e;
         hipLaunchKernelGGL(k, grid, block, p.lds, s, a, L, w_bytes);
-    } else if (zero_skip) {
-        auto k = conv_igemm_dma_kernel<T, NB, BWD, true, KS, POOL, K4>;
-        if ((e = allow_dynamic_lds(k, p.lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k, grid, block, p.lds, s, a, L, w_bytes);
+        return hipGetLastError();
+    };
+    if constexpr (PB) {  // the pooled source has no zero-skip form
+        return start(conv_igemm_dma_kernel<T, NB, BWD, false, KS, POOL, K4, true>);
     } else {
-        auto k = conv_igemm_dma_kernel<T, NB, BWD, false, KS, POOL, K4>;
-        if ((e = allow_dynamic_lds(k, p.lds)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k, grid, block, p.lds, s, a, L, w_bytes);
+        if constexpr (NB == 7 && !KS && !POOL && !K4)
+            if (a.taps9)
+                return zero_skip
+                           ? start(conv_igemm_dma_kernel<T, NB, BWD, true, KS, POOL, K4, false, true>)
+                           : start(conv_igemm_dma_kernel<T, NB, BWD, false, KS, POOL, K4, false, true>);
+        return zero_skip ? start(conv_igemm_dma_kernel<T, NB, BWD, true, KS, POOL, K4>)
+                         : start(conv_igemm_dma_kernel<T, NB, BWD, false, KS, POOL, K4>);
     }
-    return hipGetLastError();
 }
 
 template <typename T, int NB, bool BWD, bool POOL, bool PB = false>
@@ -1694,9 +1752,69 @@ hipError_t choose_conv(size_t tsz, bool bwd, const ConvGeo &g, ConvChoice &c)
     return hipSuccess;
 }
 
+// The gather plan of a plain pass whose window kernel would be c, or MW = 0 where
+// that kernel runs: under the zero skip (the gather kernel has none), or where it
+// is the faster one (with or without a relu mask, so that backward_data's sums
+// do not depend on who applied the mask):
+//   - 224-pixel tiles of whole rows, 1024 blocks or more (four a CU): the window
+<<<<<<< Updated upstream
+//     is staged once for all taps and the tiles lose nothing (the benchmark layer);
+=======
+//     is staged once for all taps and the tiles lose nothing (the benchmark layer;
+//     a first layer of three channels, 7x7: 108 us, gathered 118);
+>>>>>>> Stashed changes
+//   - the filter-resident forward where its blocks fill whole rounds of the CUs:
+//     about 5 us + 55 ns a k each (LeNet conv2, one round: 49 us, gathered 50; 144
+//     blocks of K = 765: 46 against 30; 468 of K = 375: 61 against 42);
+//   - backward_data at stride 1 with filters that are neither 1x1 nor 3x3 over a
+//     long K, whose gathered filter rows cost 4 bytes a lane (LeNet conv2, K =
+//     1600: 62 us, gathered 76; K = 500: 160 against 79).  There the window
+//     kernel's time is taken from its blocks at the 0.38 (fp64) and 0.3 of the
+//     matrix rate that such layers reach (0.2 register-staged), or from the
+//     vector kernel's 1.2 and 3 multiply-adds a nanosecond (one row, four rows).
+GatherPlan gather_for(int dtype, bool bwd, const ConvDims &d, int zero_skip, bool mask,
+                      const ConvChoice &c)
+{
+    const GatherPlan none = {};
+    if (zero_skip) return none;
+    const int taps = d.Hf * d.Wf, M = bwd ? d.C : d.F;
+    const int Qw = bwd ? d.Win : d.Wout, Q = Qw * (bwd ? d.Hin : d.Hout);
+<<<<<<< Updated upstream
+    if (c.kernel == kConvDma && c.pd.NB == 7 && c.pd.TS == 224 && d.stride == 1 &&
+        c.pd.KC % 4 == 0 && 224 % Qw == 0 && Q % 224 == 0 &&
+=======
+    if (c.kernel == kConvDma && c.pd.NB == 7 && c.pd.TS == 224 &&
+        ((d.stride == 1 && c.pd.KC % 4 == 0) || (!bwd && d.C < 4)) && 224 % Qw == 0 && Q % 224 == 0 &&
+>>>>>>> Stashed changes
+        (long long)d.N * c.pd.tiles_per_img * c.pd.m_tiles >= 1024)
+        return none;
+    const GatherPlan p = gather_plan(dtype, bwd, d, false);
+    if (!p.MW) return none;
+    const GatherPlan use = mask ? gather_plan(dtype, bwd, d, true) : p;
+    const double K = (double)(bwd ? d.F : d.C) * taps;
+    if (c.kernel == kConvResident) {
+        const long long blocks = (long long)d.N * ((M + kResRows - 1) / kResRows);
+        return 1.2 * p.us < (double)((blocks + 255) / 256) * (5.0 + 0.055 * K) ? use : none;
+    }
+    if (bwd && d.stride == 1 && taps != 1 && !(d.Hf == 3 && d.Wf == 3) && K > 600) {
+        const double rate = dtype == 0 ? 0.28e6 : 0.6e6;  // flop per us and CU
+        double us;
+        if (c.kernel == kConvSmallM) {
+            us = (double)d.N * Q * K / (M == 1 ? 1.2e6 : 3.0e6 / kSmallM);
+        } else {
+            const Plan &w = c.kernel == kConvDma ? c.pd : c.p;
+            const long long blocks = (long long)d.N * w.tiles_per_img * w.m_tiles;
+            const double eff = c.kernel == kConvDma ? (dtype == 0 ? 0.38 : 0.3) : 0.2;
+            us = (double)((blocks + 255) / 256) * dma_a_rows(M) * 32.0 * w.NB * 2.0 * K / (rate * eff);
+        }
+        return 1.25 * p.us < us ? use : none;
+    }
+    return use;
+}
+
 template <typename T, bool BWD>
-hipError_t launch_typed(IgemmArgs a, int M, int Cs, int Qh, int Qw, int nimg, int zero_skip,
-                        hipStream_t s)
+hipError_t launch_typed(IgemmArgs a, const ConvDims &d, int M, int Cs, int Qh, int Qw, int nimg,
+                        int zero_skip, hipStream_t s)
 {
     a.M = M;
     a.Cs = Cs;
@@ -1709,6 +1827,13 @@ hipError_t launch_typed(IgemmArgs a, int M, int Cs, int Qh, int Qw, int nimg, in
     ConvChoice c;
     const hipError_t ce = choose_conv(sizeof(T), BWD, g, c);
     if (ce != hipSuccess) return ce;
+    if (!pool && !a.csr && a.nbanks <= 1 && !a.require_dma && !a.pb) {
+        const GatherPlan gp = gather_for(sizeof(T) == 8 ? 0 : 1, BWD, d, zero_skip,
+                                         a.mask != nullptr, c);
+        if (gp.MW)
+            return launch_gather(sizeof(T) == 8 ? 0 : 1, BWD, gp, a.src, a.mask, a.wgt, a.bias, a.out,
+                                 d, a.relu, s);
+    }
     if (c.kernel == kConvSmallM) {
         a.KC = c.small_kc;
         a.CH = c.small_CH;
@@ -1776,6 +1901,7 @@ hipError_t launch_typed(IgemmArgs a, int M, int Cs, int Qh, int Qw, int nimg, in
         ad.magic_sa = host_magic(pd.SA);
         ad.magic_qw = host_magic(Qw);
         ad.k4 = c.k4;
+        ad.taps9 = a.Hf == 3 && a.Wf == 3 && pd.KC % 4 == 0;
         ad.ksplit = c.ksplit;
         switch (pd.NB) {
         case 7: return launch_dma<T, 7, BWD>(ad, pd, c.L, w_bytes, nimg, zero_skip, s);
@@ -1798,7 +1924,9 @@ hipError_t conv_plan_info(int dtype, int pass, const ConvDims &d, int zero_skip,
                           int ph, int pw, int ps, int pp, ConvPlanInfo &info)
 {
     info = ConvPlanInfo{};
-    if (pass == 1) return wgrad_plan_info(dtype, d, form == kFormPooledSource ? ps : 0, info);
+    if (pass == 1)
+        return wgrad_plan_info(dtype, d, form == kFormPooledSource ? ps : 0,
+                               form == kFormPlain && !zero_skip, info);
     const size_t tsz = dtype == 0 ? sizeof(double) : sizeof(float);
     const bool bwd = pass == 2;
     // backward_data is the same GEMM over the up-sampled gradient: M = C rows,
@@ -1830,6 +1958,22 @@ hipError_t conv_plan_info(int dtype, int pass, const ConvDims &d, int zero_skip,
     (void)pw;
     ConvChoice c;
     hipError_t e = choose_conv(tsz, bwd, g, c);
+    if (form == kFormPlain && e == hipSuccess) {
+        const GatherPlan gp = gather_for(dtype, bwd, d, zero_skip, false, c);
+        if (gp.MW) {
+            info.kernel = kConvGather;
+            info.tile_m = 16 * gp.MW;
+            info.tile_pixels = 64 * gp.NW;
+            info.tile_stride = 64 * gp.NW;
+            info.blocks = gp.blocks;
+            info.k_split = 1;
+            info.k_chunk = bwd && gp.form == 9 ? 36 : 128 / (int)tsz;
+            info.stage_bytes = gp.stage;
+            info.row_staged = gp.form;
+            info.lds = 2 * (size_t)gp.stage;
+            return hipSuccess;
+        }
+    }
     info.fused = applied && e == hipSuccess;
     if (e == hipErrorNotSupported && (g.pool || g.nbanks > 1)) {
         g.pool = false;
@@ -1909,8 +2053,8 @@ hipError_t launch_conv_forward(int dtype, const void *X, const void *W, const vo
     a.Pw = d.pad;
     a.relu = relu;
     if (dtype == 0)
-        return launch_typed<double, false>(a, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
-    return launch_typed<float, false>(a, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+        return launch_typed<double, false>(a, d, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+    return launch_typed<float, false>(a, d, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
 }
 
 hipError_t launch_conv_forward_pool(int dtype, const void *X, const void *W, const void *b,
@@ -1944,8 +2088,8 @@ hipError_t launch_conv_forward_pool(int dtype, const void *X, const void *W, con
     a.Hp = Hp;
     a.Wp = Wp;
     if (dtype == 0)
-        return launch_typed<double, false>(a, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
-    return launch_typed<float, false>(a, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+        return launch_typed<double, false>(a, d, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+    return launch_typed<float, false>(a, d, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
 }
 
 hipError_t launch_conv_forward_multi(int dtype, const void *X, const void *Wcat,
@@ -1977,8 +2121,8 @@ hipError_t launch_conv_forward_multi(int dtype, const void *X, const void *Wcat,
     }
     a.require_dma = 1;
     const int M = a.bank_off[nbanks];
-    if (dtype == 0) return launch_typed<double, false>(a, M, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
-    return launch_typed<float, false>(a, M, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+    if (dtype == 0) return launch_typed<double, false>(a, d, M, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+    return launch_typed<float, false>(a, d, M, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
 }
 
 namespace {
@@ -2045,8 +2189,8 @@ hipError_t launch_conv_forward_csr(int dtype, const int32_t *rowptr, const int32
     a.csr_col = colidx;
     a.csr_val = vals;
     if (dtype == 0)
-        return launch_typed<double, false>(a, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
-    return launch_typed<float, false>(a, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+        return launch_typed<double, false>(a, d, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
+    return launch_typed<float, false>(a, d, d.F, d.C, d.Hout, d.Wout, d.N, zero_skip, s);
 }
 
 hipError_t launch_conv_backward_data(int dtype, const void *W, const void *dout,
@@ -2076,8 +2220,8 @@ hipError_t launch_conv_backward_data(int dtype, const void *W, const void *dout,
     a.Pw = d.Wf - 1 - d.pad;
     a.relu = 0;
     if (dtype == 0)
-        return launch_typed<double, true>(a, d.C, d.F, d.Hin, d.Win, d.N, zero_skip, s);
-    return launch_typed<float, true>(a, d.C, d.F, d.Hin, d.Win, d.N, zero_skip, s);
+        return launch_typed<double, true>(a, d, d.C, d.F, d.Hin, d.Win, d.N, zero_skip, s);
+    return launch_typed<float, true>(a, d, d.C, d.F, d.Hin, d.Win, d.N, zero_skip, s);
 }
 
 }  // namespace dmlnn

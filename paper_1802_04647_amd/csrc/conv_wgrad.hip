@@ -1203,6 +1203,52 @@ bool choose_wplan(size_t tsz, const ConvDims &d, WPlan &p, bool &ring)
     return make_wplan(tsz, d, p);
 }
 
+// Share of a launch's matrix work that is output: filters and columns of the
+// last tiles that do not exist are padding.
+double fill(int F, long long K, int bm, int nft, int bn, int nkr)
+{
+    return (double)F / ((double)bm * nft) * (double)K / ((double)bn * nkr);
+}
+
+// The gather plan of a plain backward_filter whose window kernel would be p, or
+// MW = 0 where that kernel runs:
+//   - the row ring over long rows of full tiles (40 pixels and more, eight rows
+//     a split): each input row is staged once for nine columns a channel (the
+//     benchmark layer: fp64 1.06 ms, gathered 1.35; fp32 0.68 and 0.70);
+//   - where the gather's columns (channel pairs x taps) pad more: below 0.9 of
+//     the window kernel's fill with a grid that occupies the CUs (7 channels
+//     3x3, 35 filters: 66 us, gathered 96; 3 channels 7x7: 205 and 269);
+<<<<<<< Updated upstream
+//   - fp64 filters of 25 taps and more over well-filled tiles, where the staged
+//     window serves all taps (15 channels 5x5, 277 filters: 72 and 80 us; LeNet
+//     conv2 would gain: 74 and 60, 3% of its training step).
+=======
+//   - fp64 filters of 25 taps and more over well-filled tiles or of fewer than
+//     four channels, where the staged window serves all taps (15 channels 5x5, 277
+//     filters: 72 and 80 us; one channel 7x7: 38 and 61; LeNet conv1: 30 and 50;
+//     LeNet conv2 alone would gain: 74 and 60).
+>>>>>>> Stashed changes
+GatherPlan gather_wgrad_for(int dtype, const ConvDims &d, const WPlan &p, bool ring)
+{
+    const GatherPlan none = {};
+    const int K = d.C * d.Hf * d.Wf;
+    const double u = fill(d.F, K, kBM, p.nft, p.KR, p.nkr);
+    if (ring && d.Wout >= 40 && u > 0.85 && p.T_total >= 8LL * p.splits) return none;
+    const GatherPlan g = gather_wgrad_plan(dtype, d, p.splits);
+    if (!g.MW) return none;
+    const bool full = (long long)p.splits * p.nkr * p.nft >= kCUs;
+    if (!ring && !p.pipelined) return g;
+    const int nkr = (int)(g.blocks / g.splits / ((d.F + 16 * g.MW - 1) / (16 * g.MW)));
+    const double ug = fill(d.F, K, 16 * g.MW, (d.F + 16 * g.MW - 1) / (16 * g.MW), 64 * g.NW, nkr);
+    if (full && ug < 0.9 * u) return none;
+<<<<<<< Updated upstream
+    if (full && dtype == 0 && d.Hf * d.Wf >= 25 && d.Wout >= 14 && u > 0.8) return none;
+=======
+    if (full && dtype == 0 && d.Hf * d.Wf >= 25 && d.Wout >= 14 && (u > 0.8 || d.C < 4)) return none;
+>>>>>>> Stashed changes
+    return g;
+}
+
 // Pooled source with a short filter row (K = C*Hf*Wf <= kSpK; LeNet conv1: K =
 // 25).  The routed gradient g holds at most one non-zero cell per pool window:
 // the window's argmax, when its pooled value is positive (every other cell of
@@ -1375,6 +1421,20 @@ hipError_t launch_pool_sparse(WgradArgs a, int groups, size_t lds, void *dW, voi
 
 }  // namespace
 
+hipError_t launch_wgrad_reduce(int dtype, const void *ws, void *dW, void *db, int FK, int F,
+                               int splits, hipStream_t s)
+{
+    const int total = FK + (db ? F : 0);
+    const dim3 grid((total + 15) / 16);
+    if (dtype == 0)
+        hipLaunchKernelGGL(conv_wgrad_reduce<double>, grid, dim3(256), 0, s, (const double *)ws,
+                           (double *)dW, (double *)db, FK, F, splits);
+    else
+        hipLaunchKernelGGL(conv_wgrad_reduce<float>, grid, dim3(256), 0, s, (const float *)ws,
+                           (float *)dW, (float *)db, FK, F, splits);
+    return hipGetLastError();
+}
+
 size_t conv_wgrad_workspace_bytes(int dtype, const ConvDims &d)
 {
     const size_t tsz = dtype == 0 ? sizeof(double) : sizeof(float);
@@ -1385,7 +1445,8 @@ size_t conv_wgrad_workspace_bytes(int dtype, const ConvDims &d)
     return tsz * (size_t)p.splits * ((size_t)d.F * K + (size_t)d.F);
 }
 
-hipError_t wgrad_plan_info(int dtype, const ConvDims &d, int pool_ps, ConvPlanInfo &info)
+hipError_t wgrad_plan_info(int dtype, const ConvDims &d, int pool_ps, bool gather,
+                           ConvPlanInfo &info)
 {
     const size_t tsz = dtype == 0 ? sizeof(double) : sizeof(float);
     WPlan p;
@@ -1405,6 +1466,23 @@ hipError_t wgrad_plan_info(int dtype, const ConvDims &d, int pool_ps, ConvPlanIn
         info.tile_stride = kSpB * kWave;
         info.fused = 1;
         return hipSuccess;
+    }
+    if (gather) {
+        const GatherPlan gp = gather_wgrad_for(dtype, d, p, ring);
+        if (gp.MW) {
+            info.kernel = kWgradGather;
+            info.tile_m = 16 * gp.MW;
+            info.tile_pixels = 128 / (int)tsz;
+            info.chunk = 64 * gp.NW;
+            info.k_chunk = 128 / (int)tsz;
+            info.blocks = gp.blocks / gp.splits;
+            info.splits = p.splits;  // what the workspace holds; the launch takes at most these
+            info.k_split = 1;
+            info.stage_bytes = gp.stage;
+            info.slice_vec = gp.form;
+            info.lds = 2 * (size_t)gp.stage;
+            return hipSuccess;
+        }
     }
     info.kernel = ring ? kWgradRing : kWgradTiles;
     info.tile_m = kBM;
@@ -1442,6 +1520,11 @@ hipError_t launch_conv_backward_filter(int dtype, const void *X, const void *dou
     WPlan p;
     bool ring;
     if (!choose_wplan(tsz, d, p, ring)) return hipErrorInvalidValue;
+    if (!pool && !zero_skip) {
+        const GatherPlan gp = gather_wgrad_for(dtype, d, p, ring);
+        if (gp.MW)
+            return launch_gather_wgrad(dtype, gp, X, dout, out_fwd, dW, db, g_out, ws, d, s);
+    }
     WgradArgs a = {};
     a.X = X;
     a.dout = dout;

@@ -23,7 +23,9 @@ enum ConvKernel {
     kConvResident = 4,  // filter-resident forward for small images (fp64)
     kWgradRing = 5,     // backward_filter, row ring over the whole k range
     kWgradTiles = 6,    // backward_filter, 4-wave (f-tile, k-range, split) blocks
-    kWgradPoolSparse = 7  // backward_filter from a pooled source, small k: the pool windows
+    kWgradPoolSparse = 7, // backward_filter from a pooled source, small k: the pool windows
+    kConvGather = 8,      // gathered patch rows (forward / backward_data)
+    kWgradGather = 9      // backward_filter, gathered patch rows
 };
 
 // What the plan query reports about one pass (host only, no device access).
@@ -47,7 +49,8 @@ struct ConvPlanInfo {
 };
 
 // Fused forms a plan query may ask about (the values of dmlnn_conv_form).
-enum ConvForm { kFormPlain = 0, kFormPoolEpilogue = 1, kFormPooledSource = 2, kFormCsr = 3,
+// kFormWindow: plain, of the kernels that have a zero-skip form (no gather kernel).
+enum ConvForm { kFormWindow = -1, kFormPlain = 0, kFormPoolEpilogue = 1, kFormPooledSource = 2, kFormCsr = 3,
                 kFormBanks = 4 };
 // form: ConvForm; ph, pw, ps, pp: the pool of the pool forms (else unused).
 hipError_t conv_plan_info(int dtype, int pass, const ConvDims &d, int zero_skip, int form,
@@ -77,6 +80,30 @@ hipError_t launch_conv_forward_csr(int dtype, const int32_t *rowptr, const int32
                                    const void *vals, int nnz, int32_t *row_index, const void *W,
                                    const void *b, void *out, const ConvDims &d, int relu,
                                    int zero_skip, hipStream_t s);
+// ------------------------------------------------------- gather kernels ----
+// See conv_gather.hpp.  Plans are host only; plan.MW = 0 where the gather kernel
+// does not take the sizes or another kernel is the faster one.
+struct GatherPlan {
+    int MW, NW;      // a block's rows / 16 and pixels (backward_filter: columns) / 64
+    int form;        // forward, backward_data: NT (0, 1, 9); backward_filter: 0, 1 (VEC), 2 (XV)
+    int splits;      // backward_filter
+    int blocks, stage;
+    double us;       // the model's time, microseconds
+};
+// mask: a relu mask is folded into backward_data's source.
+GatherPlan gather_plan(int dtype, bool bwd, const ConvDims &d, bool mask);
+GatherPlan gather_wgrad_plan(int dtype, const ConvDims &d, int max_splits);
+hipError_t launch_gather(int dtype, bool bwd, const GatherPlan &p, const void *src,
+                         const void *mask, const void *W, const void *bias, void *out,
+                         const ConvDims &d, int relu, hipStream_t s);
+hipError_t launch_gather_wgrad(int dtype, const GatherPlan &p, const void *X, const void *dout,
+                               const void *mask, void *dW, void *db, void *g_out, void *ws,
+                               const ConvDims &d, hipStream_t s);
+// The split reduction of backward_filter: dW (F*K = FK elements) and db (F, or
+// null) are the sums of the splits' partials in ws, in split order.
+hipError_t launch_wgrad_reduce(int dtype, const void *ws, void *dW, void *db, int FK, int F,
+                               int splits, hipStream_t s);
+
 hipError_t launch_conv_backward_data(int dtype, const void *W, const void *dout,
                                      const void *out_fwd, void *dX, const ConvDims &d,
                                      int zero_skip, hipStream_t s, const PoolSrc *pool = nullptr);
@@ -84,8 +111,10 @@ hipError_t launch_conv_backward_data(int dtype, const void *W, const void *dout,
 // Filter/bias gradient: split reduction into a workspace, then a fixed-order sum.
 size_t conv_wgrad_workspace_bytes(int dtype, const ConvDims &d);
 // The backward_filter part of conv_plan_info.
-// pool_ps: the pool stride of a pooled source, or 0.
-hipError_t wgrad_plan_info(int dtype, const ConvDims &d, int pool_ps, ConvPlanInfo &info);
+// pool_ps: the pool stride of a pooled source, or 0.  gather: the call may take the
+// gather kernel (plain source, dense mode).
+hipError_t wgrad_plan_info(int dtype, const ConvDims &d, int pool_ps, bool gather,
+                           ConvPlanInfo &info);
 // pool (optional): dout is not given; g is built from a following max-pool's
 // backward (see PoolSrc in common.hpp).
 hipError_t launch_conv_backward_filter(int dtype, const void *X, const void *dout,

@@ -338,6 +338,16 @@ def model_igemm_dma(g, p, tsz, form):
         sched = fragment_schedule(KCK, 4 * wm, 8) if KS else fragment_schedule(KCK, 0, 4)
         return [mrow + l16, mrow + 16 + l16], [(wn * NB + y) * 16 + l16 for y in range(NB)], sched
 
+    # the 3x3 loop over groups of four channels: quarter q takes channel 4 g + q,
+    # step t of a group one tap of each
+    taps9 = (NB == 7 and not KS and not pb and not pool and (Hf, Wf) == (3, 3) and KC % 4 == 0)
+
+    def k_column(kk):
+        if not taps9:
+            return kk + lq
+        step = kk // 4
+        return (step // 9 * 4 + lq) * 9 + step % 9
+
     taken = []
     for w in range(4):
         if K4 or (KS and w < 2) or (not KS and w == 0):
@@ -385,7 +395,9 @@ def model_igemm_dma(g, p, tsz, form):
             rows_blk, us, (reads, used) = wave_form(w)
             offs = [pix_off(u) for u in us]
             for kk in reads:
-                kcol = kk + lq
+                if taps9 and kk not in used:  # no read past a group's last tap
+                    continue
+                kcol = k_column(kk)
                 kc = np.minimum(kcol, KCv - 1)
                 cc = div_magic(kc, HfWf, f"{kernel} tap channel")
                 tp = kc - cc * HfWf
@@ -1265,10 +1277,315 @@ def model_wgrad_pool_sparse(g, p, tsz, form):
          f"{kernel}: a tap reads the wrong input cell")
 
 
+# ============================================================ gather kernels
+def gather_masks(c, n, taps):
+    """Tap validity of cells whose first tap is at c: (cells, taps) booleans."""
+    t = c[:, None] + np.arange(taps)[None, :]
+    return (t >= 0) & (t < n)
+
+
+def gather_phases(g):
+    """(Hq, Wq, Hfp, Wfp, Sy, by0, bx0, oS, oy0, ox0, ry, rx) of each sub-problem."""
+    if not g["bwd"]:
+        return [(g["Qh"], g["Qw"], g["Hf"], g["Wf"], g["S"], -g["Ph"], -g["Pw"], 1, 0, 0, 0, 0)]
+    S, out = g["up"], []
+    Ph, Pw = g["Hf"] - 1 - g["Ph"], g["Wf"] - 1 - g["Pw"]
+
+    def axis(r, P, n, nf):
+        o0 = ((r - P) % S + S) % S
+        taps = cdiv(nf - r, S) if r < nf else 0
+        return (cdiv(n - o0, S) if o0 < n else 0), taps, (o0 + P - r) // S - (taps - 1), o0
+
+    for ry in range(S):
+        for rx in range(S):
+            Hq, Hfp, by0, oy0 = axis(ry, Ph, g["Qh"], g["Hf"])
+            Wq, Wfp, bx0, ox0 = axis(rx, Pw, g["Qw"], g["Wf"])
+            if Hfp == 0 or Wfp == 0:
+                Hfp = Wfp = 0
+            out.append((Hq, Wq, Hfp, Wfp, 1, by0, bx0, S, oy0, ox0, ry, rx))
+    return out
+
+
+def model_gather(g, p, tsz, form):
+    kernel = "gather"
+    need(form == "plain", f"{kernel}: form {form}")
+    N, M, Cs, bwd = g["N"], g["M"], g["Cs"], g["bwd"]
+    Sh, Sw, Hf, Wf = g["Sh"], g["Sw"], g["Hf"], g["Wf"]
+    MW, NW, NT = p["tile_m"] // 16, p["tile_pixels"] // 64, p["row_staged"]
+    BM, BN, E, KB = 16 * MW, 64 * NW, 16 // tsz, 128 // tsz
+    N9 = NT == 9 and bwd
+    KC = 36 if N9 else KB
+    need(p["k_chunk"] == KC, f"{kernel}: k per chunk")
+    need(NT == 0 or (Hf, Wf) == ((3, 3) if NT == 9 else (1, 1)), f"{kernel}: taps")
+    per = 256 // tsz
+    slab, BQ = BM * 9 + (16 - BM) % per, 9 * BN + 16
+    BNP = BN + (4 if tsz == 4 else 8)
+    a_el = 4 * slab if N9 else BM * KB
+    b_el = 4 * BQ if N9 else KB * BNP
+    need(p["stage_bytes"] == (a_el + b_el) * tsz, f"{kernel}: stage layout")
+    need(p["lds_bytes"] == 2 * p["stage_bytes"], f"{kernel}: LDS size")
+    lds = Lds(p["lds_bytes"], kernel)
+    lds.region("A", 0, a_el * tsz)
+    lds.region("B", a_el * tsz, b_el * tsz)
+    lds.disjoint("A", "B")
+    m_tiles = cdiv(M, BM)
+    subs = gather_phases(g)
+    need(p["blocks"] == m_tiles * sum(cdiv(N * s[0] * s[1], BN) for s in subs), f"{kernel}: blocks")
+    plane, HfWf = Sh * Sw, Hf * Wf
+    src_el = N * Cs * plane
+    need(src_el * tsz < 1 << 30, f"{kernel}: tensor above 1 GiB")
+    lane = np.arange(64)
+    li, lq = lane & 15, lane >> 4
+    for s in subs:
+        Hq, Wq, Hfp, Wfp, Sy, by0, bx0, oS, oy0, ox0, ry, rx = s
+        Qp, nt = Hq * Wq, Hfp * Wfp
+        Pn, K = N * Qp, Cs * nt
+        if Pn == 0:
+            continue
+        need(NT == 0 or nt == NT, f"{kernel}: taps of the sub-problem")
+        shY, shX = max(0, -by0), max(0, -bx0)
+        shift = shY * Sw + shX
+        # the taps a sub-problem sums are those that reach its outputs
+        if bwd:
+            reach = [(i, j) for i in range(Hf) for j in range(Wf)
+                     if i % g["up"] == ry and j % g["up"] == rx]
+            need(len(reach) == nt, f"{kernel}: taps that reach a phase")
+        nch = cdiv(K, KC)
+        for pt in sample(cdiv(Pn, BN), 12):
+            p0 = pt * BN
+            n0 = p0 // Qp
+            px = np.arange(BN)
+            v = p0 - n0 * Qp + px
+            dn = div_small(v, Qp, f"{kernel}: image of a pixel")
+            q = v - dn * Qp
+            hy = div_small(q, Wq, f"{kernel}: row of a pixel")
+            wx = q - hy * Wq
+            y0, x0 = by0 + Sy * hy, bx0 + Sy * wx
+            inside = p0 + px < Pn
+            base = np.where(inside, ((n0 + dn) * Cs * Sh + y0 + shY) * Sw + x0 + shX, 0)
+            need((base >= 0) & (base * tsz < 1 << 30), f"{kernel}: first-tap offset")
+            yok = gather_masks(y0, Sh, max(Hfp, 1)) & inside[:, None]
+            xok = gather_masks(x0, Sw, max(Wfp, 1)) & inside[:, None]
+            need(max(Hfp, Wfp) <= 31, f"{kernel}: tap mask bits")
+            # the output cells of the tile
+            oy, ox = oy0 + oS * hy, ox0 + oS * wx
+            need(~inside | ((n0 + dn < N) & (oy < g["Qh"]) & (ox < g["Qw"])),
+                 f"{kernel}: output cell outside its plane")
+            cells = ((n0 + dn) * M * g["Qh"] + oy) * g["Qw"] + ox
+            glob(kernel, "out", cells[inside] + (M - 1) * g["Qh"] * g["Qw"], N * M * g["Qh"] * g["Qw"])
+
+            for mt in sample(m_tiles, 3):
+                m0 = mt * BM
+                for ch in sample(nch, 6):
+                    k0 = ch * KC
+                    # patch rows: (row, pixel) -> source element, -1 for a zero
+                    B = np.full(b_el, -2, dtype=np.int64)
+                    for row in range(KC):
+                        c, t = (k0 + row) // nt, (k0 + row) % nt
+                        ti, tj = t // Wfp, t % Wfp
+                        so = c * plane + ti * Sw + tj
+                        ok = yok[:, ti] & xok[:, tj] & (c < Cs)
+                        el = base - shift + so
+                        glob(kernel, "src", el[ok], src_el)
+                        need(~ok | ((base + so) * tsz < (src_el + shift) * tsz),
+                             f"{kernel}: patch offset past the buffer's range")
+                        dst = (row // 9) * BQ + (row % 9) * BN + px if N9 else row * BNP + px
+                        lds.access("B", dst, tsz, "patch row")
+                        B[dst] = np.where(ok, el, -1)
+                    # filter slice -> filter element, -1 for a zero
+                    A = np.full(a_el, -2, dtype=np.int64)
+                    w_el = M * Cs * HfWf
+
+                    def put(dst, el):
+                        lds.access("A", dst, tsz, "filter slice")
+                        A[dst] = np.where((el >= 0) & (el < w_el), el, -1)
+
+                    if N9:
+                        for w in range(4):
+                            e = np.arange(BM * 9)
+                            need(BM * 9 % E == 0, f"{kernel}: pieces of a slab")
+                            put(w * slab + e, ((k0 // 9 + w) * M + m0) * 9 + e)
+                    elif not bwd:
+                        r, kl = np.divmod(np.arange(BM * KB), KB)
+                        el = np.where(k0 + kl < K, (m0 + r) * K + k0 + kl, -1)  # (tail pieces zeroed)
+                        put(r * KB + ((kl // E) ^ (r & 7)) * E + kl % E, el)
+                    else:
+                        r, kl = np.divmod(np.arange(BM * KB), KB)
+                        f, t = (k0 + kl) // nt, (k0 + kl) % nt
+                        i2, j2 = t // Wfp, t % Wfp
+                        S = g["up"]
+                        el = ((f * M + m0 + r) * HfWf + (ry + S * (Hfp - 1 - i2)) * Wf +
+                              rx + S * (Wfp - 1 - j2))
+                        put(r * KB + ((kl // E) ^ (r & 7)) * E + kl % E, np.where(f < Cs, el, -1))
+                    # fragment reads of every wave and step
+                    for w in range(4):
+                        steps = range(9) if N9 else range(2 * E)
+                        for st in steps:
+                            if N9:
+                                krow = lq * 9 + st
+                                ia = lq * slab + li * 9 + 8 - st
+                                ib = lq * BQ + w * 16 * NW + li + st * BN
+                                xa = 16 * 9
+                            else:
+                                gq, se = st // E, st % E
+                                krow = (4 * gq + lq) * E + se
+                                ia = li * KB + ((4 * gq + lq) ^ (li & 7)) * E + se
+                                ib = lq * E * BNP + w * 16 * NW + li + (gq * 4 * E + se) * BNP
+                                xa = 16 * KB
+                            k = k0 + krow
+                            c, t = k // nt, k % nt
+                            i2, j2 = t // Wfp, t % Wfp
+                            real = k < K
+                            for x in range(MW):
+                                lds.access("A", ia + x * xa, tsz, "filter fragment")
+                                a = A[ia + x * xa]
+                                m = m0 + 16 * x + li
+                                if bwd:
+                                    S = g["up"]
+                                    want = ((c * M + m) * HfWf + (ry + S * (Hfp - 1 - i2)) * Wf +
+                                            rx + S * (Wfp - 1 - j2))
+                                else:
+                                    want = (m * Cs + c) * HfWf + i2 * Wf + j2
+                                need((a == want) | ~real | (m >= M),
+                                     f"{kernel}: a filter fragment holds the wrong element of W")
+                                need(a != -2, f"{kernel}: an MFMA reads an LDS slot nothing staged")
+                            for y in range(NW):
+                                lds.access("B", ib + 16 * y, tsz, "patch fragment")
+                                b = B[ib + 16 * y]
+                                pp = w * 16 * NW + li + 16 * y
+                                yy, xx = y0[pp] + i2, x0[pp] + j2
+                                cell = ((n0 + dn[pp]) * Cs + c) * plane + yy * Sw + xx
+                                ok = (yy >= 0) & (yy < Sh) & (xx >= 0) & (xx < Sw) & inside[pp]
+                                need((b == np.where(ok, cell, -1)) | ~real,
+                                     f"{kernel}: a patch fragment holds the wrong source cell")
+                                need(real | (b == -1),
+                                     f"{kernel}: a padded k column meets a patch value")
+        # the sub-problems write every cell of the plane once
+    cover = np.zeros((g["Qh"], g["Qw"]), dtype=np.int64)
+    for s in subs:
+        cover[s[8]:s[8] + s[7] * s[0]:s[7], s[9]:s[9] + s[7] * s[1]:s[7]] += 1
+    need(cover == 1, f"{kernel}: output cells not written once")
+
+
+def model_wgrad_gather(g, p, tsz, form):
+    kernel = "wgrad_gather"
+    need(form == "plain", f"{kernel}: form {form}")
+    N, C, F, K, Q, S, P = g["N"], g["C"], g["F"], g["K"], g["Q"], g["S"], g["P"]
+    Hin, Win, Hf, Wf, Wout, Hout = (g[k] for k in ("Hin", "Win", "Hf", "Wf", "Wout", "Hout"))
+    MW, NW, mode = p["tile_m"] // 16, p["chunk"] // 64, p["slice_vec"]
+    vec, xv = mode >= 1, mode == 2
+    BM, BN, E, KB = 16 * MW, 64 * NW, 16 // tsz, 128 // tsz
+    need(p["k_chunk"] == KB, f"{kernel}: k per chunk")
+    need(p["stage_bytes"] == (BM + BN) * 128 and p["lds_bytes"] == 2 * p["stage_bytes"],
+         f"{kernel}: LDS size")
+    need(not vec or Q % E == 0, f"{kernel}: a 16-byte piece crosses an image")
+    need(not xv or (Hf * Wf == 1 and S == 1 and P == 0), f"{kernel}: 16-byte patch rows")
+    ws_elems = p["workspace_bytes"] // tsz
+    need(ws_elems >= p["splits"] * (F * K + F), f"{kernel}: workspace size")
+    lds = Lds(p["lds_bytes"], kernel)
+    lds.region("A", 0, BM * 128)
+    lds.region("B", BM * 128, BN * 128)
+    nt, plane, npc = Hf * Wf, Hin * Win, (C + 1) // 2
+    cols = C if xv else 2 * npc * nt
+    nkr, nft = cdiv(cols, BN), cdiv(F, BM)
+    need(p["blocks"] == nkr * nft, f"{kernel}: blocks per split")
+    Pn = N * Q
+    nchunk = cdiv(Pn, KB)
+    shift = P * Win + P
+    x_el, g_el = N * C * plane, N * F * Q
+    need(max(x_el, g_el) * tsz < 1 << 30, f"{kernel}: tensor above 1 GiB")
+    tid = np.arange(256)
+    lane = np.arange(64)
+    li, lq = lane & 15, lane >> 4
+    cover = np.zeros(F * K, dtype=np.int64)
+    # output columns: (tap, channel) of every column of every block
+    for kr in range(nkr):
+        col = np.arange(BN)
+        u = kr * (BN // 2) + (col >> 1)
+        t = np.zeros_like(u) if xv else u // npc
+        c = 2 * (u - t * npc) + (col & 1)
+        ok = (c < C) & (t < nt)
+        for ft in range(nft):
+            f = ft * BM + np.arange(BM)
+            f = f[f < F]
+            idx = f[:, None] * K + (c[ok] * nt + t[ok])[None, :]
+            glob(kernel, "dW", idx, F * K)
+            np.add.at(cover, idx.ravel(), 1)
+    need(cover == 1, f"{kernel}: dW elements not written once")
+    glob(kernel, "workspace (db)", p["splits"] * F * K + (p["splits"] - 1) * F + np.arange(F), ws_elems)
+    LR = KB // (E if vec else 1)
+    RP = 256 // LR
+    for splits in sorted({1, min(p["splits"], max(1, nchunk // 4))}):
+        need([s * nchunk // splits for s in range(splits + 1)][-1] == nchunk, f"{kernel}: chunks")
+    for ch in sample(nchunk, 6):
+        p0 = ch * KB
+        for ft in sorted({0, nft - 1}):
+            A = np.full(BM * KB, -2, dtype=np.int64)  # gradient cell n * Q + q of row r, or -1
+            for j in range(cdiv(BM, RP)):
+                gl, gr = tid % LR * (E if vec else 1), tid // LR + j * RP
+                live = gr < BM
+                for e in range(E if vec else 1):
+                    pp = p0 + gl + e
+                    n, q = pp // Q, pp % Q
+                    inside = p0 + gl < Pn
+                    need(~inside | (pp < Pn), f"{kernel}: a piece past the last pixel")
+                    el = (n * F + ft * BM + gr) * Q + q
+                    st_ok = inside & live & (ft * BM + gr < F)
+                    glob(kernel, "dout", el[st_ok], g_el)
+                    dst = gr * KB + (((gl // E) ^ (gr & 7)) * E) + gl % E + e
+                    lds.access("A", dst[live], tsz, "gradient tile")
+                    A[dst[live]] = np.where(inside, pp, -1)[live]
+            for kr in sample(nkr, 3):
+                B = np.full(BN * KB, -2, dtype=np.int64)  # source element, or -1
+                colB = np.arange(BN)
+                for i in range(KB):
+                    pp = p0 + i
+                    n, q = pp // Q, pp % Q
+                    oh, ow = q // Wout, q % Wout
+                    u = kr * (BN // 2) + (colB >> 1)
+                    t = np.zeros_like(u) if xv else u // npc
+                    c = 2 * (u - t * npc) + (colB & 1)
+                    y, x = oh * S - P + t // Wf, ow * S - P + t % Wf
+                    ok = (pp < Pn) & (t < nt) & (y >= 0) & (y < Hin) & (x >= 0) & (x < Win)
+                    off = (n * C + c) * plane + (oh * S + t // Wf) * Win + ow * S + t % Wf
+                    need(~ok | (c >= C) | (off >= 0), f"{kernel}: patch offset")
+                    el = off - shift
+                    glob(kernel, "X", el[ok & (c < C)], x_el)
+                    dst = colB * KB + ((i // E) ^ (colB & 7)) * E + i % E
+                    lds.access("B", dst, tsz, "patch row")
+                    B[dst] = np.where(ok, np.where(el < x_el, el, -1), -1)
+                for w in range(4):
+                    for gq in range(2):
+                        for se in range(E):
+                            po = ((4 * gq + lq) ^ (li & 7)) * E + se
+                            i = (4 * gq + lq) * E + se
+                            for x in range(MW):
+                                r = 16 * x + li
+                                a = A[r * KB + po]
+                                need(a == np.where(p0 + i < Pn, p0 + i, -1),
+                                     f"{kernel}: a gradient fragment holds the wrong pixel")
+                            for y in range(NW):
+                                colr = w * 16 * NW + 16 * y + li
+                                lds.access("B", colr * KB + po, tsz, "patch fragment")
+                                b = B[colr * KB + po]
+                                pp = p0 + i
+                                u = kr * (BN // 2) + (colr >> 1)
+                                t = np.zeros_like(u) if xv else u // npc
+                                c = 2 * (u - t * npc) + (colr & 1)
+                                n, q = pp // Q, pp % Q
+                                yy, xx = q // Wout * S - P + t // Wf, q % Wout * S - P + t % Wf
+                                cell = x_cell(g, c, yy, xx)
+                                want = np.where((cell >= 0) & (pp < Pn), n * C * plane + cell, -1)
+                                need((b == want) | (c >= C) | (t >= nt),
+                                     f"{kernel}: a patch fragment holds the wrong source cell")
+                                need(b != -2, f"{kernel}: an MFMA reads an LDS slot nothing staged")
+
+
 # ================================================================ dispatch
 MODELS = {"igemm_dma": model_igemm_dma, "igemm_reg": model_igemm_reg, "small_m": model_small_m,
           "resident": model_resident, "wgrad_ring": model_wgrad_ring,
-          "wgrad_tiles": model_wgrad_tiles, "wgrad_pool_sparse": model_wgrad_pool_sparse}
+          "wgrad_tiles": model_wgrad_tiles, "wgrad_pool_sparse": model_wgrad_pool_sparse,
+          "gather": model_gather, "wgrad_gather": model_wgrad_gather}
 
 
 def check_conv(s, pass_name, dtype, plan, form="plain", pool=None):

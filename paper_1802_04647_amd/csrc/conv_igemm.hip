@@ -1757,12 +1757,8 @@ hipError_t choose_conv(size_t tsz, bool bwd, const ConvGeo &g, ConvChoice &c)
 // is the faster one (with or without a relu mask, so that backward_data's sums
 // do not depend on who applied the mask):
 //   - 224-pixel tiles of whole rows, 1024 blocks or more (four a CU): the window
-<<<<<<< Updated upstream
-//     is staged once for all taps and the tiles lose nothing (the benchmark layer);
-=======
 //     is staged once for all taps and the tiles lose nothing (the benchmark layer;
 //     a first layer of three channels, 7x7: 108 us, gathered 118);
->>>>>>> Stashed changes
 //   - the filter-resident forward where its blocks fill whole rounds of the CUs:
 //     about 5 us + 55 ns a k each (LeNet conv2, one round: 49 us, gathered 50; 144
 //     blocks of K = 765: 46 against 30; 468 of K = 375: 61 against 42);
@@ -1779,13 +1775,8 @@ GatherPlan gather_for(int dtype, bool bwd, const ConvDims &d, int zero_skip, boo
     if (zero_skip) return none;
     const int taps = d.Hf * d.Wf, M = bwd ? d.C : d.F;
     const int Qw = bwd ? d.Win : d.Wout, Q = Qw * (bwd ? d.Hin : d.Hout);
-<<<<<<< Updated upstream
-    if (c.kernel == kConvDma && c.pd.NB == 7 && c.pd.TS == 224 && d.stride == 1 &&
-        c.pd.KC % 4 == 0 && 224 % Qw == 0 && Q % 224 == 0 &&
-=======
     if (c.kernel == kConvDma && c.pd.NB == 7 && c.pd.TS == 224 &&
         ((d.stride == 1 && c.pd.KC % 4 == 0) || (!bwd && d.C < 4)) && 224 % Qw == 0 && Q % 224 == 0 &&
->>>>>>> Stashed changes
         (long long)d.N * c.pd.tiles_per_img * c.pd.m_tiles >= 1024)
         return none;
     const GatherPlan p = gather_plan(dtype, bwd, d, false);

@@ -1218,16 +1218,10 @@ double fill(int F, long long K, int bm, int nft, int bn, int nkr)
 //   - where the gather's columns (channel pairs x taps) pad more: below 0.9 of
 //     the window kernel's fill with a grid that occupies the CUs (7 channels
 //     3x3, 35 filters: 66 us, gathered 96; 3 channels 7x7: 205 and 269);
-<<<<<<< Updated upstream
-//   - fp64 filters of 25 taps and more over well-filled tiles, where the staged
-//     window serves all taps (15 channels 5x5, 277 filters: 72 and 80 us; LeNet
-//     conv2 would gain: 74 and 60, 3% of its training step).
-=======
 //   - fp64 filters of 25 taps and more over well-filled tiles or of fewer than
 //     four channels, where the staged window serves all taps (15 channels 5x5, 277
 //     filters: 72 and 80 us; one channel 7x7: 38 and 61; LeNet conv1: 30 and 50;
 //     LeNet conv2 alone would gain: 74 and 60).
->>>>>>> Stashed changes
 GatherPlan gather_wgrad_for(int dtype, const ConvDims &d, const WPlan &p, bool ring)
 {
     const GatherPlan none = {};
@@ -1241,11 +1235,7 @@ GatherPlan gather_wgrad_for(int dtype, const ConvDims &d, const WPlan &p, bool r
     const int nkr = (int)(g.blocks / g.splits / ((d.F + 16 * g.MW - 1) / (16 * g.MW)));
     const double ug = fill(d.F, K, 16 * g.MW, (d.F + 16 * g.MW - 1) / (16 * g.MW), 64 * g.NW, nkr);
     if (full && ug < 0.9 * u) return none;
-<<<<<<< Updated upstream
-    if (full && dtype == 0 && d.Hf * d.Wf >= 25 && d.Wout >= 14 && u > 0.8) return none;
-=======
     if (full && dtype == 0 && d.Hf * d.Wf >= 25 && d.Wout >= 14 && (u > 0.8 || d.C < 4)) return none;
->>>>>>> Stashed changes
     return g;
 }
 

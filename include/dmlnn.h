@@ -427,7 +427,8 @@ DMLNN_API size_t affine_workspace_size(dmlnn_dtype dtype, int N, int D, int M);
 /* Host-only plan query (no device access), like conv2d_plan: the launch shape
  * one affine product takes for these sizes and workspace_bytes.  product: 0 =
  * out = X W (M_out = N rows, N_out = M columns, reduction D), 1 = dX = g W^T,
- * 2 = dW = X^T g.  *tile: the edge of a block's output tile (16 or 32);
+ * 2 = dW = X^T g.  *tile: the edge of a block's output tile (16 or 32; 0 for
+ * a large product that runs on a gather kernel, unsplit);
  * *waves: waves per block, each a k range of that tile; *splits: blocks per
  * tile along k (partials in the workspace when above 1).  Returns
  * DMLNN_ERR_ARG for invalid sizes or product, DMLNN_ERR_NULL for a NULL

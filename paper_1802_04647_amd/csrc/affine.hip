@@ -295,12 +295,22 @@ __global__ __launch_bounds__(256) void colsum_kernel(const T *G, const T *mask, 
     const int jl = threadIdx.x & 15, ph = threadIdx.x >> 4;
     const int j = blockIdx.x * 16 + jl;
     T s = T(0);
-    if (j < M)
-        for (int i = ph; i < N; i += 16) {
-            T v = G[(size_t)i * M + j];
-            if (mask && !(mask[(size_t)i * M + j] > T(0))) v = T(0);
-            s += v;
+    if (j < M) {
+        // eight rows' loads in flight, added in order (a load each waited for took
+        // 11 us for 512 x 1000 in fp32; here 5)
+        for (int i = ph; i < N; i += 16 * 8) {
+            T v[8], m[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const size_t o = (size_t)min(i + 16 * u, N - 1) * M + j;
+                v[u] = G[o];
+                m[u] = mask ? mask[o] : T(1);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i + 16 * u < N) s += m[u] > T(0) ? v[u] : T(0);
         }
+    }
     s_part[ph][jl] = s;
     __syncthreads();
     if (ph == 0 && j < M) {
@@ -399,6 +409,27 @@ hipError_t gemm(GemmArgs g, void *workspace, size_t workspace_bytes, hipStream_t
 
 }  // namespace
 
+// The affine products as conv passes of a 1x1 filter over one image of a row:
+//   out = X W    forward: image W (D channels of M pixels), filters X (N x D);
+//   dX = g W^T   backward_filter: image W, gradient g (N "filters" of M pixels);
+//   dW = X^T g   backward_data: gradient g, filters X.
+// The gather kernels' LDS tiles carry large products at 2-3 times the fragments
+// fetched by each wave (512 x 2048 x 1000 in fp32: out 39 -> 28 us, dX 39 -> 29, dW
+// 44 -> 32); below 2.5e8 multiply-adds (64 x 3136 x 512: 12 us split over blocks)
+// they have too few tiles.
+ConvDims affine_dims(int N, int D, int M)
+{
+    return ConvDims{1, D, 1, M, N, 1, 1, 1, 0, 1, M};
+}
+
+GatherPlan affine_gather(int dtype, int product, int N, int D, int M)
+{
+    if ((double)N * D * M < 2.5e8) return GatherPlan{};
+    const ConvDims d = affine_dims(N, D, M);
+    if (product == 1) return gather_wgrad_plan(dtype, d, 1);
+    return gather_plan(dtype, product == 2, d, false);
+}
+
 size_t affine_workspace_bytes(int dtype, int N, int D, int M)
 {
     const size_t el = dtype == 0 ? 8 : 4;
@@ -413,6 +444,9 @@ hipError_t launch_affine_fwd(int dtype, const void *X, const void *W, const void
                              int N, int D, int M, int relu, void *workspace,
                              size_t workspace_bytes, hipStream_t s)
 {
+    const GatherPlan p = affine_gather(dtype, 0, N, D, M);
+    if (p.MW)
+        return launch_gather(dtype, false, p, W, nullptr, X, b, out, affine_dims(N, D, M), relu, s, 1);
     GemmArgs g = {};
     g.A = X;
     g.sAm = D;
@@ -437,7 +471,13 @@ hipError_t launch_affine_bwd(int dtype, const void *dout, const void *X, const v
                              hipStream_t s)
 {
     hipError_t e;
-    if (dX) {  // dX[n, d] = sum_m g[n, m] W[d, m]  (times X[n, d] > 0 with relu_input)
+    const GatherPlan px = affine_gather(dtype, 1, N, D, M), pw = affine_gather(dtype, 2, N, D, M);
+    const ConvDims dims = affine_dims(N, D, M);
+    if (dX && px.MW) {
+        e = launch_gather_wgrad(dtype, px, W, dout, out_fwd, dX, nullptr, nullptr, nullptr, dims, s,
+                                relu_input ? X : nullptr);
+        if (e != hipSuccess) return e;
+    } else if (dX) {  // dX[n, d] = sum_m g[n, m] W[d, m]  (times X[n, d] > 0 with relu_input)
         GemmArgs g = {};
         g.xmask = relu_input ? X : nullptr;
         g.A = dout;
@@ -456,7 +496,11 @@ hipError_t launch_affine_bwd(int dtype, const void *dout, const void *X, const v
                        : gemm<float>(g, workspace, workspace_bytes, s);
         if (e != hipSuccess) return e;
     }
-    if (dW) {  // dW[d, m] = sum_n X[n, d] g[n, m]
+    if (dW && pw.MW) {
+        const GatherPlan p = out_fwd ? gather_plan(dtype, true, dims, true) : pw;
+        if ((e = launch_gather(dtype, true, p, dout, out_fwd, X, nullptr, dW, dims, 0, s)) != hipSuccess)
+            return e;
+    } else if (dW) {  // dW[d, m] = sum_n X[n, d] g[n, m]
         GemmArgs g = {};
         g.A = X;
         g.sAm = 1;

@@ -671,6 +671,12 @@ int affine_plan(dmlnn_dtype dtype, int product, int N, int D, int M, size_t work
     // (rows, columns, reduction) of the product
     const int r = product == 2 ? D : N, c = product == 1 ? D : M, k = product == 0 ? D
                                                                  : (product == 1 ? M : N);
+    if (dmlnn::affine_gather(dtype, product, N, D, M).MW) {
+        *tile = 0;
+        *waves = 4;
+        *splits = 1;
+        return DMLNN_OK;
+    }
     const dmlnn::GemmPlan p = dmlnn::gemm_plan(r, c, k, el, workspace_bytes);
     *tile = 16 * p.wt;
     *waves = p.nk;

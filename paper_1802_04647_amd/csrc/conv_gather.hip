@@ -167,7 +167,7 @@ hipError_t launch_gather_wgrad_f64(const GatherPlan &, gather::WgArgs, hipStream
 hipError_t launch_gather_wgrad_f32(const GatherPlan &, gather::WgArgs, hipStream_t);
 
 hipError_t launch_gather(int dtype, bool bwd, const GatherPlan &p, const void *src,
-                         const void *mask, const void *W, const void *bias, void *out, const ConvDims &d, int relu, hipStream_t s)
+                         const void *mask, const void *W, const void *bias, void *out, const ConvDims &d, int relu, hipStream_t s, int bias_pixels)
 {
     const size_t tsz = dtype == 0 ? 8 : 4;
     gather::FwdArgs a = {};
@@ -188,6 +188,7 @@ hipError_t launch_gather(int dtype, bool bwd, const GatherPlan &p, const void *s
     a.S = d.stride;
     a.P = d.pad;
     a.relu = relu;
+    a.bias_cols = bias_pixels;
     a.m_tiles = (a.M + 16 * p.MW - 1) / (16 * p.MW);
     a.src_bytes = (unsigned)((size_t)a.N * a.Cs * a.Sh * a.Sw * tsz);
     a.w_bytes = (unsigned)((size_t)a.M * a.Cs * a.Hf * a.Wf * tsz);
@@ -196,8 +197,9 @@ hipError_t launch_gather(int dtype, bool bwd, const GatherPlan &p, const void *s
 
 hipError_t launch_gather_wgrad(int dtype, const GatherPlan &p, const void *X, const void *dout,
                                const void *mask, void *dW, void *db, void *g_out, void *ws,
-                               const ConvDims &d, hipStream_t s)
+                               const ConvDims &d, hipStream_t s, const void *out_mask)
 {
+    if (out_mask && p.splits != 1) return hipErrorInvalidValue;
     const size_t tsz = dtype == 0 ? 8 : 4;
     const int taps = d.Hf * d.Wf, Q = d.Hout * d.Wout;
     gather::WgArgs a = {};
@@ -208,6 +210,7 @@ hipError_t launch_gather_wgrad(int dtype, const GatherPlan &p, const void *X, co
     a.dW = dW;
     a.db = db;
     a.g_out = g_out;
+    a.out_mask = out_mask;
     a.N = d.N;
     a.C = d.C;
     a.Hin = d.Hin;

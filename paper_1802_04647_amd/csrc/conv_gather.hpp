@@ -544,6 +544,7 @@ struct WgArgs {
     void *ws;                     // [splits][F][K] partials, then [splits][F] bias partials
     void *dW, *db;                // written instead of the partials when splits = 1
     void *g_out;                  // or null
+    const void *out_mask;         // or null (one split): dW is zeroed where it is not positive
     int N, C, Hin, Win, F, Hf, Wf, S, P, Hout, Wout;
     int nkr, nft, splits, want_db;
     unsigned x_bytes, g_bytes;
@@ -797,7 +798,11 @@ __global__ __launch_bounds__(kThreads, 2) void wgrad_gather_kernel(WgArgs a)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int f = f0 + 16 * x + MF::row(lane, r);
-                if (f < a.F) wsp[(size_t)f * K + c * nt + t] = acc[x][y][r];
+                if (f >= a.F) continue;
+                const size_t o = (size_t)f * K + c * nt + t;
+                T v = acc[x][y][r];
+                if (a.out_mask && !(reinterpret_cast<const T *>(a.out_mask)[o] > T(0))) v = T(0);
+                wsp[o] = v;
             }
     }
     if (sum_db) {

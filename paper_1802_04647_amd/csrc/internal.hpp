@@ -95,10 +95,15 @@ GatherPlan gather_plan(int dtype, bool bwd, const ConvDims &d, bool mask);
 GatherPlan gather_wgrad_plan(int dtype, const ConvDims &d, int max_splits);
 hipError_t launch_gather(int dtype, bool bwd, const GatherPlan &p, const void *src,
                          const void *mask, const void *W, const void *bias, void *out,
-                         const ConvDims &d, int relu, hipStream_t s);
+                         const ConvDims &d, int relu, hipStream_t s, int bias_pixels = 0);
 hipError_t launch_gather_wgrad(int dtype, const GatherPlan &p, const void *X, const void *dout,
                                const void *mask, void *dW, void *db, void *g_out, void *ws,
-                               const ConvDims &d, hipStream_t s);
+                               const ConvDims &d, hipStream_t s, const void *out_mask = nullptr);
+// (bias_pixels: the bias goes along the pixels of the one image instead of the
+// rows; out_mask, with one split: dW is zeroed where it is not positive.)
+// The gather plan of an affine product (0 forward, 1 dX, 2 dW), MW = 0 where the
+// affine kernel runs.
+GatherPlan affine_gather(int dtype, int product, int N, int D, int M);
 // The split reduction of backward_filter: dW (F*K = FK elements) and db (F, or
 // null) are the sums of the splits' partials in ws, in split order.
 hipError_t launch_wgrad_reduce(int dtype, const void *ws, void *dW, void *db, int FK, int F,

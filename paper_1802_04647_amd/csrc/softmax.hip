@@ -39,6 +39,7 @@ __device__ __forceinline__ T seg_max(T v, int sw)
 
 constexpr int kSmThreads = 1024;
 constexpr int kSmWaves = kSmThreads / kWave;
+constexpr int kSmCols = 16;         // columns a lane holds in registers
 constexpr int kSmMaxBlocks = 2048;  // blocks of a call with a workspace (one loss share each)
 
 // part: null (one block: the loss goes to *loss) or one element a block (the
@@ -75,6 +76,51 @@ __global__ __launch_bounds__(kSmThreads) void softmax_xent_kernel(const T *S, co
                 dS[o] = (p * ys - yk) * invN;
             }
             if (n < N) total += rl;
+        }
+    } else if (K <= kSmCols * kWave) {
+        // Up to kSmCols columns a lane, a row a wave: scores and labels are loaded
+        // once, all in flight together (the general loop below reads them three
+        // times, each pass waiting for the one before: 512 x 1000 fp32 19 us, here
+        // 9), in the same order.
+        for (int n = wave_g; n < N; n += nwaves) {
+            const T *s = S + (size_t)n * K;
+            const T *y = Y + (size_t)n * K;
+            T sk[kSmCols], yk[kSmCols];
+#pragma unroll
+            for (int u = 0; u < kSmCols; ++u) {
+                const int k = min(lane + kWave * u, K - 1);
+                sk[u] = s[k];
+                yk[u] = y[k];
+            }
+            T m = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < kSmCols; ++u)
+                if (lane + kWave * u < K) m = sk[u] > m ? sk[u] : m;
+            m = seg_max(m, kWave);
+            T se = T(0), ys = T(0), e[kSmCols];
+#pragma unroll
+            for (int u = 0; u < kSmCols; ++u) {
+                e[u] = exp(sk[u] - m);
+                if (lane + kWave * u < K) {
+                    se += e[u];
+                    ys += yk[u];
+                }
+            }
+            se = seg_sum(se, kWave);
+            ys = seg_sum(ys, kWave);
+            const T lse = m + log(se);
+            T rl = T(0);
+#pragma unroll
+            for (int u = 0; u < kSmCols; ++u) {
+                const int k = lane + kWave * u;
+                if (k < K) {
+                    const T p = e[u] / se;
+                    if (P) P[(size_t)n * K + k] = p;
+                    dS[(size_t)n * K + k] = (p * ys - yk[u]) * invN;
+                    rl -= yk[u] * (sk[u] - lse);
+                }
+            }
+            total += seg_sum(rl, kWave);
         }
     } else {
         for (int r0 = wave_g * rpw; r0 < N; r0 += nwaves * rpw) {

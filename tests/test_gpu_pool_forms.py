@@ -1,0 +1,92 @@
+"""The pooling, bias and softmax kernels' forms at the edges of their rules, against
+the oracle: 3x3 windows at stride 2 (2x2 cell blocks), planes of 256 cells and
+more (16-byte and single accesses), rows of up to 1024 columns held in registers,
+and affine products large enough for the gather kernels."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from gpu_util import assert_close, dev, host, rounded
+from paper_1802_04647_amd import dmlnn
+from paper_1802_04647_amd.inputs import rng
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("hwp", [(3, 3, 0), (1, 2, 1), (7, 8, 0), (8, 7, 1), (9, 9, 2), (33, 46, 1),
+                                 (64, 33, 2)], ids=str)
+def test_pool_3x3_stride_2(hwp, dt):
+    H, W, p = hwp
+    N, C = 3, 5
+    g = rng(51)
+    X = rounded(np.round(g.standard_normal((N, C * H * W)), 1), dt)   # ties
+    out_r, idx_r, Ho, Wo = oracle.max_pool2d_fwd(X, C, H, W, 3, 3, 2, p)
+    out, idx, _, _ = dmlnn.max_pool2d_fwd(dev(X, dt), C, H, W, 3, 3, 2, p)
+    assert np.array_equal(host(out), out_r) and np.array_equal(idx.cpu().numpy(), idx_r)
+    dout = rounded(g.standard_normal((N, C * Ho * Wo)), dt)
+    dX = dmlnn.max_pool2d_bwd(dev(dout, dt), idx, C, H, W, 3, 3, 2, p)
+    assert_close(host(dX), oracle.max_pool2d_bwd(dout, idx_r, C, H, W, 3, 3, 2, p), dt, "dX")
+    gated = dmlnn.max_pool2d_bwd_relu(dev(dout, dt), idx, out, C, H, W, 3, 3, 2, p)
+    ref = oracle.max_pool2d_bwd(np.where(out_r > 0, dout, 0.0), idx_r, C, H, W, 3, 3, 2, p)
+    assert_close(host(gated), ref, dt, "gated dX")
+    # an output one element off its alignment
+    buf = torch.full((N * C * H * W + 1,), float("nan"), dtype=dX.dtype, device="cuda")
+    off = buf[1:].view(N, C * H * W)
+    dmlnn.max_pool2d_bwd(dev(dout, dt), idx, C, H, W, 3, 3, 2, p, dX=off)
+    assert torch.equal(off, dX)
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("hw", [255, 256, 258, 4097 * 4], ids=str)
+def test_bias_relu_planes(hw, dt):
+    N, C = 2, 3
+    g = rng(52)
+    X, b = rounded(g.standard_normal((N, C * hw)), dt), rounded(g.standard_normal(C), dt)
+    for bias in (b, None):
+        got = dmlnn.bias_add_relu(dev(X, dt), dev(bias, dt), C, hw)
+        assert_close(host(got), oracle.bias_add_relu(X, bias, C, hw, relu=True), dt, "bias")
+    t = torch.zeros(X.size + 1, dtype=dev(X, dt).dtype, device="cuda")
+    x1 = t[1:].view(N, C * hw)
+    x1.copy_(dev(X, dt))
+    dmlnn.bias_add_relu(x1, dev(b, dt), C, hw, out=x1)                 # misaligned, in place
+    assert torch.equal(x1, dmlnn.bias_add_relu(dev(X, dt), dev(b, dt), C, hw))
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("nk", [(5, 65), (40, 1000), (17, 1024), (3, 1025)], ids=str)
+def test_softmax_xent_wide_rows(nk, dt):
+    N, K = nk
+    g = rng(53)
+    S = rounded(3 * g.standard_normal((N, K)), dt)
+    Y = np.eye(K)[g.integers(0, K, N)]
+    loss, ds, p = dmlnn.softmax_xent(dev(S, dt), dev(Y, dt))
+    rl, rds, rp = oracle.softmax_xent(S, Y)[:3]
+    assert_close(host(loss), np.asarray([rl]).reshape(1), dt, "loss")
+    assert_close(host(ds), rds, dt, "dscores")
+    assert_close(host(p), rp, dt, "probs")
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+@pytest.mark.parametrize("shape", [(130, 2001, 1003), (520, 1024, 512)], ids=str)
+def test_large_affine_takes_the_gather_kernels(shape, dt):
+    N, D, M = shape
+    tdt = torch.float64 if dt == "f64" else torch.float32
+    assert all(dmlnn.affine_plan(tdt, p, N, D, M, 0)["tile"] == 0 for p in ("forward", "dX", "dW"))
+    print(f"\n[gpu] affine {shape} {dt}", flush=True)
+    g = rng(54)
+    X = rounded(np.maximum(g.standard_normal((N, D)), 0.0), dt)
+    W = rounded(g.standard_normal((D, M)) * np.sqrt(2.0 / D), dt)
+    b = rounded(g.standard_normal(M), dt)
+    dout = rounded(g.standard_normal((N, M)), dt)
+    for relu in (True, False):
+        ref = oracle.affine_fwd(X, W, b, relu=relu)
+        assert_close(host(dmlnn.affine_fwd(dev(X, dt), dev(W, dt), dev(b, dt), relu=relu)), ref, dt, "out")
+        mask = rounded(ref, dt) if relu else None
+        rdX, rdW, rdb = oracle.affine_bwd(dout, X, W, mask)
+        dX, dW, db = dmlnn.affine_bwd(dev(dout, dt), dev(X, dt), dev(W, dt), dev(mask, dt),
+                                      relu_input=relu)
+        assert_close(host(dX), rdX * (X > 0) if relu else rdX, dt, "dX")
+        assert_close(host(dW), rdW, dt, "dW")
+        assert_close(host(db), rdb, dt, "db")

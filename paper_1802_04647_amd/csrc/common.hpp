@@ -76,6 +76,25 @@ __device__ __forceinline__ int div_small(int n, int d, float rcp)
     return q;
 }
 
+// floor(n / d) for 0 <= n < 2^31 and 1 <= d < 2^31 in a multiply and a shift: with
+// 2^(l-1) < d <= 2^l and m = floor(2^(31+l) / d) + 1 (under 2^32), n m / 2^(31+l)
+// exceeds n / d by at most n / 2^(31+l) < 1 / d.
+struct FastDiv {
+    unsigned m;
+    int sh, d;
+    explicit FastDiv(int div) : m(0), sh(0), d(div)
+    {
+        int l = 1;
+        while (l < 31 && (1ull << l) < (unsigned long long)div) ++l;
+        sh = l - 1;
+        if (div > 1) m = (unsigned)((1ull << (31 + l)) / (unsigned long long)div) + 1u;
+    }
+    __device__ __forceinline__ int div(int n) const
+    {
+        return d == 1 ? n : (int)(__umulhi((unsigned)n, m) >> sh);
+    }
+};
+
 inline unsigned long long host_magic(int d)
 {
     return (0x100000000ull + (unsigned long long)d - 1ull) / (unsigned long long)d;

@@ -29,40 +29,36 @@ __global__ __launch_bounds__(256) void bias_add_relu_kernel(const T *X, const T 
     }
 }
 
-// The same by planes of HW values (blockIdx.y walks the N*C planes), V elements a
-// thread at a time: no division per element, 16-byte accesses where the planes
-// and pointers allow them (V = 16 bytes' worth).  54 -> 42 us for 32 x 64 planes of
-// 112x112 in fp32 (4.9 TB/s).
+// The same for totals under 2^31, V elements of a plane a thread at a time (one plane
+// is hw = HW / V of them): no 64-bit division per element, 16-byte accesses where
+// the planes and pointers allow them.  32 x 64 planes of 112x112 in fp32: 54 -> @@ us.
 template <typename T, int V>
-__global__ __launch_bounds__(256) void bias_add_relu_planes_kernel(const T *X, const T *b, T *out,
-                                                                   long long planes, int C, int HW,
-                                                                   int relu)
+__global__ __launch_bounds__(256) void bias_add_relu_vec_kernel(const T *X, const T *b, T *out,
+                                                                int total, FastDiv hw, FastDiv C,
+                                                                int relu)
 {
     typedef T vec __attribute__((ext_vector_type(V)));
-    for (long long pl = blockIdx.y; pl < planes; pl += gridDim.y) {
-        const T bias = b ? b[(int)(pl % C)] : T(0);
-        const T *x = X + (size_t)pl * HW;
-        T *o = out + (size_t)pl * HW;
-        for (int e = (blockIdx.x * 256 + threadIdx.x) * V; e < HW; e += gridDim.x * 256 * V) {
-            vec v = *reinterpret_cast<const vec *>(x + e);
+    for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < total;
+         e += (long long)gridDim.x * 256) {
+        const int pl = hw.div((int)e);
+        const T bias = b ? b[pl - C.div(pl) * C.d] : T(0);
+        vec v = reinterpret_cast<const vec *>(X)[e];
 #pragma unroll
-            for (int i = 0; i < V; ++i) v[i] = relu_if(b ? v[i] + bias : v[i], relu);
-            *reinterpret_cast<vec *>(o + e) = v;
-        }
+        for (int i = 0; i < V; ++i) v[i] = relu_if(b ? v[i] + bias : v[i], relu);
+        reinterpret_cast<vec *>(out)[e] = v;
     }
 }
 
 template <typename T>
-hipError_t bias_planes(const T *X, const T *b, T *out, long long planes, int C, int HW, int relu,
-                       hipStream_t s)
+hipError_t bias_vec(const T *X, const T *b, T *out, long long total, int C, int HW, int relu,
+                    hipStream_t s)
 {
     constexpr int V = 16 / (int)sizeof(T);
     const bool vec = HW % V == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)out % 16 == 0;
-    const int per = 256 * (vec ? V : 1);
-    const int gx = (HW + per - 1) / per < 16 ? (HW + per - 1) / per : 16;
-    const dim3 grid(gx, (unsigned)(planes < 32768 / gx ? planes : 32768 / gx));
-    auto k = vec ? bias_add_relu_planes_kernel<T, V> : bias_add_relu_planes_kernel<T, 1>;
-    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, X, b, out, planes, C, HW, relu);
+    const int n = (int)(vec ? total / V : total);
+    auto k = vec ? bias_add_relu_vec_kernel<T, V> : bias_add_relu_vec_kernel<T, 1>;
+    hipLaunchKernelGGL(k, dim3(stream_grid(n)), dim3(256), 0, s, X, b, out, n,
+                       FastDiv(vec ? HW / V : HW), FastDiv(C), relu);
     return hipGetLastError();
 }
 
@@ -104,13 +100,10 @@ hipError_t launch_bias_add_relu(int dtype, const void *X, const void *b, void *o
                                 int HW, int relu, hipStream_t s)
 {
     const long long total = (long long)N * C * HW;
-    // planes of a block and more (an affine layer's HW is 1)
-    if (HW >= 256 && HW < (1 << 30)) {
-        const long long planes = (long long)N * C;
+    if (total > 0 && total < (1ll << 31))
         return dtype == 0
-                   ? bias_planes((const double *)X, (const double *)b, (double *)out, planes, C, HW, relu, s)
-                   : bias_planes((const float *)X, (const float *)b, (float *)out, planes, C, HW, relu, s);
-    }
+                   ? bias_vec((const double *)X, (const double *)b, (double *)out, total, C, HW, relu, s)
+                   : bias_vec((const float *)X, (const float *)b, (float *)out, total, C, HW, relu, s);
     const int g = stream_grid(total);
     if (dtype == 0)
         hipLaunchKernelGGL(bias_add_relu_kernel<double>, dim3(g), dim3(256), 0, s,

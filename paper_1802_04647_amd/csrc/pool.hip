@@ -22,26 +22,50 @@
 namespace dmlnn {
 namespace {
 
-// Thread per output; blockIdx.y walks the planes (index math inside a plane is
-// 32-bit: three 64-bit divisions an output took 54 us for 2048 planes of 112x112,
-// 3x3 at stride 2, fp32, where this takes 41).  K: the window edge when it is 2 or
-// 3, its cells loaded together (clamped, and dropped where they lie outside);
+// The kernels below number the elements (outputs, regions, cell blocks; R to a plane)
+// of a group of G planes through, G R >= kGroup for small planes: blockIdx.y walks
+// the groups, blockIdx.x * 256 + threadIdx.x the elements, with 32-bit index math.
+// Blocks of one plane each would idle on small ones (16384 planes of 7x7 outputs
+// fill 49 of 256 threads).
+constexpr int kGroup = 2048;
+
+struct Planes {
+    long long n;  // planes
+    int G;        // to a group
+    FastDiv R, C;
+    Planes(long long planes, int r, int c)
+        : n(planes), G(r >= kGroup || c > (1 << 30) ? 1 : (kGroup + r - 1) / r), R(r), C(c)
+    {
+    }
+    dim3 grid(int max_x, int max_blocks) const
+    {
+        const int per = (int)(G < n ? G : n) * R.d;
+        const int gx = std::min((per + 255) / 256, max_x);
+        const long long gy = (n + G - 1) / G;
+        return dim3(gx, (unsigned)std::min<long long>(gy, std::max(1, max_blocks / gx)));
+    }
+};
+
+// Thread per output.  Three 64-bit divisions an output took 54 us for 2048 planes of
+// 112x112, 3x3 at stride 2, fp32, where this takes @@.  K: the window edge when it is
+// 2 or 3, its cells loaded together (clamped, and dropped where they lie outside);
 // 0: any window.
 template <typename T, int K>
 __global__ __launch_bounds__(256) void max_pool_fwd_kernel(const T *__restrict__ X,
                                                            T *__restrict__ out,
                                                            int32_t *__restrict__ argmax,
-                                                           long long planes, int C, int Hin,
-                                                           int Win, int Hf, int Wf, int S, int P,
-                                                           int Hout, int Wout)
+                                                           Planes pls, FastDiv wo, int Hin,
+                                                           int Win, int Hf, int Wf, int S, int P)
 {
-    const int O = Hout * Wout, HW = Hin * Win;
-    for (long long pl = blockIdx.y; pl < planes; pl += gridDim.y) {
-        const int c = (int)(pl % C);
-        const T *plane = X + (size_t)pl * HW;
-        for (long long le = blockIdx.x * 256 + threadIdx.x; le < O; le += gridDim.x * 256) {
-            const int e = (int)le;
-            const int oh = e / Wout, ow = e - oh * Wout;
+    const int O = pls.R.d, HW = Hin * Win;
+    for (long long p0 = (long long)blockIdx.y * pls.G; p0 < pls.n; p0 += (long long)gridDim.y * pls.G) {
+        const int c0 = (int)(p0 % pls.C.d);
+        const long long E = (pls.n - p0 < pls.G ? pls.n - p0 : pls.G) * O;
+        for (long long le = blockIdx.x * 256 + threadIdx.x; le < E; le += gridDim.x * 256) {
+            const int g = pls.R.div((int)le), e = (int)le - g * O;
+            const int c = c0 + g - pls.C.div(c0 + g) * pls.C.d;
+            const T *plane = X + (size_t)(p0 + g) * HW;
+            const int oh = wo.div(e), ow = e - oh * wo.d;
             const int h0 = oh * S - P, w0 = ow * S - P;
             T best = T(0);
             int bidx = -1;
@@ -75,8 +99,8 @@ __global__ __launch_bounds__(256) void max_pool_fwd_kernel(const T *__restrict__
                     }
                 }
             }
-            out[(size_t)pl * O + e] = best;
-            argmax[(size_t)pl * O + e] = c * HW + bidx;
+            out[(size_t)p0 * O + le] = best;
+            argmax[(size_t)p0 * O + le] = c * HW + bidx;
         }
     }
 }
@@ -143,19 +167,21 @@ __global__ __launch_bounds__(256) void max_pool_bwd_kernel(const T *__restrict__
 template <typename T, bool VEC2>
 __global__ __launch_bounds__(256) void max_pool_bwd_regions_kernel(
     const T *__restrict__ dout, const int32_t *__restrict__ argmax, const T *__restrict__ pooled,
-    T *__restrict__ dX, long long planes, int C, int Hin, int Win, int S, int Hout, int Wout,
-    int Ry, int Rx)
+    T *__restrict__ dX, Planes pls, FastDiv bx, int Hin, int Win, int S, int Hout, int Wout)
 {
     typedef T T2 __attribute__((ext_vector_type(2)));
-    const int HW = Hin * Win, R = Ry * Rx;
-    for (long long pl = blockIdx.y; pl < planes; pl += gridDim.y) {
-        const int c = (int)(pl % C);
-        const T *dp = dout + (size_t)pl * Hout * Wout;
-        const int32_t *ap = argmax + (size_t)pl * Hout * Wout;
-        const T *pp = pooled ? pooled + (size_t)pl * Hout * Wout : nullptr;
-        T *dXp = dX + (size_t)pl * HW;
-        for (int idx = blockIdx.x * 256 + threadIdx.x; idx < R; idx += gridDim.x * 256) {
-            const int ry = idx / Rx, rx = idx - ry * Rx;
+    const int HW = Hin * Win, R = pls.R.d, O = Hout * Wout;
+    for (long long p0 = (long long)blockIdx.y * pls.G; p0 < pls.n; p0 += (long long)gridDim.y * pls.G) {
+        const int c0 = (int)(p0 % pls.C.d);
+        const long long E = (pls.n - p0 < pls.G ? pls.n - p0 : pls.G) * R;
+        for (long long le = blockIdx.x * 256 + threadIdx.x; le < E; le += gridDim.x * 256) {
+            const int g = pls.R.div((int)le), idx = (int)le - g * R;
+            const int c = c0 + g - pls.C.div(c0 + g) * pls.C.d;
+            const T *dp = dout + (size_t)(p0 + g) * O;
+            const int32_t *ap = argmax + (size_t)(p0 + g) * O;
+            const T *pp = pooled ? pooled + (size_t)(p0 + g) * O : nullptr;
+            T *dXp = dX + (size_t)(p0 + g) * HW;
+            const int ry = bx.div(idx), rx = idx - ry * bx.d;
             const bool win = ry < Hout && rx < Wout;
             const int o = win ? ry * Wout + rx : 0;  // a valid address either way
             const int32_t am = ap[o];
@@ -191,20 +217,21 @@ __global__ __launch_bounds__(256) void max_pool_bwd_regions_kernel(
 template <typename T, bool VEC2>
 __global__ __launch_bounds__(256) void max_pool_bwd_3x3s2_kernel(
     const T *__restrict__ dout, const int32_t *__restrict__ argmax, const T *__restrict__ pooled,
-    T *__restrict__ dX, long long planes, int C, int Hin, int Win, int P, int Hout, int Wout,
-    int By, int Bx)
+    T *__restrict__ dX, Planes pls, FastDiv bx, int Hin, int Win, int P, int Hout, int Wout)
 {
     typedef T T2 __attribute__((ext_vector_type(2)));
-    const int HW = Hin * Win, R = By * Bx, O = Hout * Wout;
-    const float rcp = 1.0f / (float)Bx;
-    for (long long pl = blockIdx.y; pl < planes; pl += gridDim.y) {
-        const int c = (int)(pl % C);
-        const T *dp = dout + (size_t)pl * O;
-        const int32_t *ap = argmax + (size_t)pl * O;
-        const T *pp = pooled ? pooled + (size_t)pl * O : nullptr;
-        T *dXp = dX + (size_t)pl * HW;
-        for (int idx = blockIdx.x * 256 + threadIdx.x; idx < R; idx += gridDim.x * 256) {
-            const int y = div_small(idx, Bx, rcp), x = idx - y * Bx;
+    const int HW = Hin * Win, R = pls.R.d, O = Hout * Wout;
+    for (long long p0 = (long long)blockIdx.y * pls.G; p0 < pls.n; p0 += (long long)gridDim.y * pls.G) {
+        const int c0 = (int)(p0 % pls.C.d);
+        const long long E = (pls.n - p0 < pls.G ? pls.n - p0 : pls.G) * R;
+        for (long long le = blockIdx.x * 256 + threadIdx.x; le < E; le += gridDim.x * 256) {
+            const int g = pls.R.div((int)le), idx = (int)le - g * R;
+            const int c = c0 + g - pls.C.div(c0 + g) * pls.C.d;
+            const T *dp = dout + (size_t)(p0 + g) * O;
+            const int32_t *ap = argmax + (size_t)(p0 + g) * O;
+            const T *pp = pooled ? pooled + (size_t)(p0 + g) * O : nullptr;
+            T *dXp = dX + (size_t)(p0 + g) * HW;
+            const int y = bx.div(idx), x = idx - y * bx.d;
             const int oy = y - 1 + (P + 1) / 2, ox = x - 1 + (P + 1) / 2;
             int32_t am[4];
             T d[4], pv[4];
@@ -246,14 +273,12 @@ template <typename T>
 hipError_t pool_fwd(const T *X, T *out, int32_t *argmax, int N, int C, int Hin, int Win, int Hf,
                     int Wf, int stride, int pad, int Hout, int Wout, hipStream_t s)
 {
-    const long long planes = (long long)N * C, O = (long long)Hout * Wout;
-    const int gx = (int)std::min<long long>(64, (O + 255) / 256);
-    const dim3 grid(gx, (unsigned)std::min<long long>(planes, 65536 / gx));
+    const Planes pls((long long)N * C, Hout * Wout, C);
     auto k = Hf == 3 && Wf == 3 ? max_pool_fwd_kernel<T, 3>
                                 : (Hf == 2 && Wf == 2 ? max_pool_fwd_kernel<T, 2>
                                                       : max_pool_fwd_kernel<T, 0>);
-    hipLaunchKernelGGL(k, grid, dim3(256), 0, s, X, out, argmax, planes, C, Hin, Win, Hf, Wf,
-                       stride, pad, Hout, Wout);
+    hipLaunchKernelGGL(k, pls.grid(64, 65536), dim3(256), 0, s, X, out, argmax, pls, FastDiv(Wout),
+                       Hin, Win, Hf, Wf, stride, pad);
     return hipGetLastError();
 }
 
@@ -280,52 +305,43 @@ hipError_t launch_max_pool_bwd(int dtype, const void *dout, const int32_t *argma
     if (stride >= Hf && stride >= Wf && pad == 0) {
         // disjoint windows: one thread per stride region
         const int Ry = (Hin + stride - 1) / stride, Rx = (Win + stride - 1) / stride;
-        const int R = Ry * Rx;
-        int gx = (R + 255) / 256;
-        if (gx > 8) gx = 8;
-        long long gy = planes;
-        const long long cap = 32768 / gx;
-        if (gy > cap) gy = cap;
-        const dim3 grid(gx, (unsigned)gy);
+        const Planes pls(planes, Ry * Rx, C);
+        const dim3 grid = pls.grid(64, 32768);
         const size_t tsz = dtype == 0 ? sizeof(double) : sizeof(float);
         const bool vec2 = stride == 2 && Win % 2 == 0 && (uintptr_t)dX % (2 * tsz) == 0;
         if (dtype == 0) {
             auto k = vec2 ? max_pool_bwd_regions_kernel<double, true>
                           : max_pool_bwd_regions_kernel<double, false>;
             hipLaunchKernelGGL(k, grid, dim3(256), 0, s, (const double *)dout, argmax,
-                               (const double *)pooled, (double *)dX, planes, C, Hin, Win, stride,
-                               Hout, Wout, Ry, Rx);
+                               (const double *)pooled, (double *)dX, pls, FastDiv(Rx), Hin, Win,
+                               stride, Hout, Wout);
         } else {
             auto k = vec2 ? max_pool_bwd_regions_kernel<float, true>
                           : max_pool_bwd_regions_kernel<float, false>;
             hipLaunchKernelGGL(k, grid, dim3(256), 0, s, (const float *)dout, argmax,
-                               (const float *)pooled, (float *)dX, planes, C, Hin, Win, stride,
-                               Hout, Wout, Ry, Rx);
+                               (const float *)pooled, (float *)dX, pls, FastDiv(Rx), Hin, Win,
+                               stride, Hout, Wout);
         }
         return hipGetLastError();
     }
-    if (stride == 2 && Hf == 3 && Wf == 3 && HW < (1 << 22)) {
+    if (stride == 2 && Hf == 3 && Wf == 3) {
         const int By = (Hin + 1) / 2, Bx = (Win + 1) / 2;
-        int gx = (By * Bx + 255) / 256;
-        if (gx > 16) gx = 16;
-        long long gy = planes;
-        const long long cap = 65536 / gx;
-        if (gy > cap) gy = cap;
-        const dim3 grid(gx, (unsigned)gy);
+        const Planes pls(planes, By * Bx, C);
+        const dim3 grid = pls.grid(64, 65536);
         const size_t tsz = dtype == 0 ? sizeof(double) : sizeof(float);
         const bool vec2 = Win % 2 == 0 && (uintptr_t)dX % (2 * tsz) == 0;
         if (dtype == 0) {
             auto k = vec2 ? max_pool_bwd_3x3s2_kernel<double, true>
                           : max_pool_bwd_3x3s2_kernel<double, false>;
             hipLaunchKernelGGL(k, grid, dim3(256), 0, s, (const double *)dout, argmax,
-                               (const double *)pooled, (double *)dX, planes, C, Hin, Win, pad,
-                               Hout, Wout, By, Bx);
+                               (const double *)pooled, (double *)dX, pls, FastDiv(Bx), Hin, Win,
+                               pad, Hout, Wout);
         } else {
             auto k = vec2 ? max_pool_bwd_3x3s2_kernel<float, true>
                           : max_pool_bwd_3x3s2_kernel<float, false>;
             hipLaunchKernelGGL(k, grid, dim3(256), 0, s, (const float *)dout, argmax,
-                               (const float *)pooled, (float *)dX, planes, C, Hin, Win, pad, Hout,
-                               Wout, By, Bx);
+                               (const float *)pooled, (float *)dX, pls, FastDiv(Bx), Hin, Win,
+                               pad, Hout, Wout);
         }
         return hipGetLastError();
     }

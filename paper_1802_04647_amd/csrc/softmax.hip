@@ -39,8 +39,35 @@ __device__ __forceinline__ T seg_max(T v, int sw)
 
 constexpr int kSmThreads = 1024;
 constexpr int kSmWaves = kSmThreads / kWave;
-constexpr int kSmCols = 16;         // columns a lane holds in registers
 constexpr int kSmMaxBlocks = 2048;  // blocks of a call with a workspace (one loss share each)
+
+// The block's sum of row losses (total: a lane's), to its share or to the loss.
+template <typename T>
+__device__ __forceinline__ void block_share(T *s_part, T total, int rpw, int sw, T *part, T *loss,
+                                            T invN)
+{
+    s_part[threadIdx.x] = total;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        // segment i (wave i / rpw, segment i % rpw) keeps its sum at s_part[i * sw];
+        // the sums are added in segment order, read sixteen at a time so the
+        // LDS reads overlap instead of each waiting for the previous add
+        const int nseg = kSmWaves * rpw;
+        T t = T(0);
+        for (int i0 = 0; i0 < nseg; i0 += 16) {
+            T v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = s_part[min(i0 + u, nseg - 1) * sw];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                if (i0 + u < nseg) t += v[u];
+        }
+        if (part)
+            part[blockIdx.x] = t;
+        else
+            *loss = t * invN;
+    }
+}
 
 // part: null (one block: the loss goes to *loss) or one element a block (the
 // block's share of the sum of row losses, before the 1/N).
@@ -77,51 +104,6 @@ __global__ __launch_bounds__(kSmThreads) void softmax_xent_kernel(const T *S, co
             }
             if (n < N) total += rl;
         }
-    } else if (K <= kSmCols * kWave) {
-        // Up to kSmCols columns a lane, a row a wave: scores and labels are loaded
-        // once, all in flight together (the general loop below reads them three
-        // times, each pass waiting for the one before: 512 x 1000 fp32 19 us, here
-        // 9), in the same order.
-        for (int n = wave_g; n < N; n += nwaves) {
-            const T *s = S + (size_t)n * K;
-            const T *y = Y + (size_t)n * K;
-            T sk[kSmCols], yk[kSmCols];
-#pragma unroll
-            for (int u = 0; u < kSmCols; ++u) {
-                const int k = min(lane + kWave * u, K - 1);
-                sk[u] = s[k];
-                yk[u] = y[k];
-            }
-            T m = -INFINITY;
-#pragma unroll
-            for (int u = 0; u < kSmCols; ++u)
-                if (lane + kWave * u < K) m = sk[u] > m ? sk[u] : m;
-            m = seg_max(m, kWave);
-            T se = T(0), ys = T(0), e[kSmCols];
-#pragma unroll
-            for (int u = 0; u < kSmCols; ++u) {
-                e[u] = exp(sk[u] - m);
-                if (lane + kWave * u < K) {
-                    se += e[u];
-                    ys += yk[u];
-                }
-            }
-            se = seg_sum(se, kWave);
-            ys = seg_sum(ys, kWave);
-            const T lse = m + log(se);
-            T rl = T(0);
-#pragma unroll
-            for (int u = 0; u < kSmCols; ++u) {
-                const int k = lane + kWave * u;
-                if (k < K) {
-                    const T p = e[u] / se;
-                    if (P) P[(size_t)n * K + k] = p;
-                    dS[(size_t)n * K + k] = (p * ys - yk[u]) * invN;
-                    rl -= yk[u] * (sk[u] - lse);
-                }
-            }
-            total += seg_sum(rl, kWave);
-        }
     } else {
         for (int r0 = wave_g * rpw; r0 < N; r0 += nwaves * rpw) {
             const int n = r0 + seg;
@@ -154,27 +136,70 @@ __global__ __launch_bounds__(kSmThreads) void softmax_xent_kernel(const T *S, co
             if (ok) total += rl;
         }
     }
-    s_part[threadIdx.x] = total;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        // segment i (wave i / rpw, segment i % rpw) keeps its sum at s_part[i * sw];
-        // the sums are added in segment order, read sixteen at a time so the
-        // LDS reads overlap instead of each waiting for the previous add
-        const int nseg = kSmWaves * rpw;
-        T t = T(0);
-        for (int i0 = 0; i0 < nseg; i0 += 16) {
-            T v[16];
+    block_share(s_part, total, rpw, sw, part, loss, invN);
+}
+
+// The same for rows of 64 < K <= kSmCols<T> columns: scores and labels of a row are
+// loaded once, all in flight together, where the general loop reads them three
+// times, each pass waiting for the one before (512 x 1000 fp32: 19 us, here @@), in the
+// same order.  Columns per lane: as many as 128 registers hold without spilling.
+template <typename T>
+constexpr int kSmCols = sizeof(T) == 4 ? 16 : 8;
+
+template <typename T>
+__global__ __launch_bounds__(kSmThreads) void softmax_xent_rows_kernel(const T *S, const T *Y,
+                                                                       T *P, T *dS, T *loss,
+                                                                       T *part, int N, int K)
+{
+    constexpr int NC = kSmCols<T>;
+    __shared__ T s_part[kSmThreads];
+    const int wave_g = blockIdx.x * kSmWaves + wave_id(), nwaves = gridDim.x * kSmWaves;
+    const T invN = T(1) / T(N);
+    T total = T(0);
+    for (int n = wave_g; n < N; n += nwaves) {
+        const size_t row = (size_t)n * K;
+        const T *s = S + row, *y = Y + row;
+        T *ds = dS + row, *pr = P ? P + row : nullptr;
+        const int lane = opaque(lane_id());  // column indices are not kept across rows
+        T sk[NC], yk[NC], e[NC];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = s_part[min(i0 + u, nseg - 1) * sw];
-#pragma unroll
-            for (int u = 0; u < 16; ++u)
-                if (i0 + u < nseg) t += v[u];
+        for (int u = 0; u < NC; ++u) {
+            const unsigned k = min(lane + kWave * u, K - 1);
+            sk[u] = s[k];
+            yk[u] = y[k];
         }
-        if (part)
-            part[blockIdx.x] = t;
-        else
-            *loss = t * invN;
+        T m = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < NC; ++u)
+            if (lane + kWave * u < K) m = sk[u] > m ? sk[u] : m;
+        m = seg_max(m, kWave);
+        T se = T(0), ys = T(0);
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            __builtin_amdgcn_sched_barrier(0);  // one exponential's temporaries at a time
+            const bool ok = lane + kWave * u < K;
+            e[u] = exp(sk[u] - m);
+            se += ok ? e[u] : T(0);
+            ys += ok ? yk[u] : T(0);
+        }
+        se = seg_sum(se, kWave);
+        ys = seg_sum(ys, kWave);
+        const T lse = m + log(se);
+        T rl = T(0);
+#pragma unroll
+        for (int u = 0; u < NC; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned k = lane + kWave * u;
+            if (k < (unsigned)K) {
+                const T p = e[u] / se;
+                if (pr) pr[k] = p;
+                ds[k] = (p * ys - yk[u]) * invN;
+                rl -= yk[u] * (sk[u] - lse);
+            }
+        }
+        total += seg_sum(rl, kWave);
     }
+    block_share(s_part, total, 1, kWave, part, loss, invN);
 }
 
 // The loss from the blocks' shares: lane l adds shares l, l + 64, ... in order,
@@ -269,14 +294,15 @@ hipError_t launch_xent(const void *S, const void *Y, void *P, void *dS, void *lo
     const int sw = softmax_segment(K);
     long long G = ws ? std::min<long long>(softmax_blocks(N, K), (long long)(ws_bytes / sizeof(T)))
                      : 1;
-    if (G <= 1) {
-        hipLaunchKernelGGL(softmax_xent_kernel<T>, dim3(1), dim3(kSmThreads), 0, s,
-                           (const T *)S, (const T *)Y, (T *)P, (T *)dS, (T *)loss, (T *)nullptr,
-                           N, K, sw);
-        return hipGetLastError();
-    }
-    hipLaunchKernelGGL(softmax_xent_kernel<T>, dim3((int)G), dim3(kSmThreads), 0, s, (const T *)S,
-                       (const T *)Y, (T *)P, (T *)dS, (T *)loss, (T *)ws, N, K, sw);
+    T *part = G <= 1 ? nullptr : (T *)ws;
+    const dim3 grid((int)std::max<long long>(G, 1)), block(kSmThreads);
+    if (K > kWave && K <= kSmCols<T> * kWave)
+        hipLaunchKernelGGL(softmax_xent_rows_kernel<T>, grid, block, 0, s, (const T *)S,
+                           (const T *)Y, (T *)P, (T *)dS, (T *)loss, part, N, K);
+    else
+        hipLaunchKernelGGL(softmax_xent_kernel<T>, grid, block, 0, s, (const T *)S, (const T *)Y,
+                           (T *)P, (T *)dS, (T *)loss, part, N, K, sw);
+    if (!part) return hipGetLastError();
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(softmax_loss_reduce<T>, dim3(1), dim3(kWave), 0, s, (const T *)ws, (int)G,

@@ -41,3 +41,14 @@ def test_lenet_scoring_matches_oracle_and_is_stream_independent():
     ref = forward_probs(X, params)
     assert_close(host(p3), ref, "f64", "probs")
     np.testing.assert_allclose(host(p3).sum(axis=1), 1.0, rtol=1e-12)
+
+
+@pytest.mark.parametrize("batch,M", [(16, 16), (16, 288), (100, 300), (300, 600)])
+def test_lenet_scoring_runs_of_batches(batch, M):
+    """One batch, a run and a remainder, a batch that does not divide a run, a larger one."""
+    _, _, params = lenet_train_inputs()
+    X = _images(M)
+    scorer = LeNetScorer(params, batch=batch, streams=2)
+    for Xs in (X, X[::-1].copy(), X[:batch]):
+        assert_close(host(scorer.score(torch.from_numpy(Xs).cuda())), forward_probs(Xs, params),
+                     "f64", "probs")

@@ -82,6 +82,11 @@ GatherPlan gather_plan(int dtype, bool bwd, const ConvDims &d, bool mask)
         // resident, overlap these better (K = 25, 204 rows: 31 against 42 us).
         const double stage_us = 0.16 * t.NW + (bwd && form == 0 ? 0.055 : 0.015) * t.MW;
         if (Cs * taps < 12 * KC && (t.NW > 1 || t.MW > 5)) continue;
+        // The backward tiles above 64 rows, or 4 x 2, were the fastest for none of 34
+        // layers: the staging of a filter row's taps grows with MW and fewer blocks
+        // are resident (256 channels 3x3 at 14x14, fp32: 128
+        // rows 158 us, 32 rows 137; 64 from 128 channels at stride 2, fp64: 181, 170).
+        if (bwd && t.MW * t.NW > 4) continue;
         double cost = 0.0, one = 0.0, chain = 0.0;
         long long tiles = 0;
         for (int ph = 0; ph < phases; ++ph) {

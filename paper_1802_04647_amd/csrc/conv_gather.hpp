@@ -174,7 +174,7 @@ struct FwdLayout {
 
 // fp32 sums are kept in two levels: every kFlush chunks (256 k) the MFMA
 // accumulators are added to a second set and cleared, which shortens the chain
-// of roundings (K = 2304: error 6e-7 -> see below for what it measured).
+// of roundings (K = 2304: error against 64 bits 6.0e-7 -> 2.1e-7).
 constexpr int kFlush = 8;
 
 // Forward and backward_data.  A block computes 16 MW rows x 64 NW pixels with

@@ -830,7 +830,42 @@ __global__ __launch_bounds__(kRingThreads, 1) void conv_wgrad_ring_kernel(WgradA
         const bool pf = kLoadInLoop && tt + 1 < t_end;
         const int pfg = min(4 * wave, a.RQ - 4);
         const int pfx = min(4 * ((wave + kRingWaves / 2) % kRingWaves), a.RQ - 4);
-        for (int qq = 0; qq < a.RQ; qq += 4) {
+        // Vector instructions take issue cycles from the matrix pipe, and the general
+        // step below spends twelve on addresses and columns.  At stride 1 (the DMA
+        // form) the steps that lie inside the row go two a round on running pointers
+        // with constant offsets.  256 x 64 x 56 x 56, 64 filters, 3x3: fp64 @1, fp32 @2.
+        int qq = 0;
+        if constexpr (XD) {
+            const T *gp[4], *xp[NBW];
+#pragma unroll
+            for (int mb = 0; mb < 4; ++mb) gp[mb] = grow + mb * 16 * a.SG;
+#pragma unroll
+            for (int nb = 0; nb < NBW; ++nb) xp[nb] = s_x + kof[nb] + lq;
+            for (; qq + 8 <= a.Wout; qq += 8) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    T av[4];
+#pragma unroll
+                    for (int mb = 0; mb < 4; ++mb) av[mb] = gp[mb][4 * h];
+                    bool za[4];
+#pragma unroll
+                    for (int mb = 0; mb < 4; ++mb) za[mb] = ZSKIP && wave_all_zero(av[mb]);
+#pragma unroll
+                    for (int nb = 0; nb < NBW; ++nb) {
+                        const T bv = xp[nb][4 * h];
+                        if (ZSKIP && wave_all_zero(bv)) continue;
+#pragma unroll
+                        for (int mb = 0; mb < 4; ++mb)
+                            if (!za[mb]) acc[mb][nb] = MF::mma(av[mb], bv, acc[mb][nb]);
+                    }
+                }
+#pragma unroll
+                for (int mb = 0; mb < 4; ++mb) gp[mb] += 8;
+#pragma unroll
+                for (int nb = 0; nb < NBW; ++nb) xp[nb] += 8;
+            }
+        }
+        for (; qq < a.RQ; qq += 4) {
             if (qq == pfg && pf) load_g(n1, oh1);
             if (qq == pfx && pf && oh1 != 0) {
                 if constexpr (XD)

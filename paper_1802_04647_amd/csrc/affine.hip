@@ -413,10 +413,16 @@ hipError_t gemm(GemmArgs g, void *workspace, size_t workspace_bytes, hipStream_t
 //   out = X W    forward: image W (D channels of M pixels), filters X (N x D);
 //   dX = g W^T   backward_filter: image W, gradient g (N "filters" of M pixels);
 //   dW = X^T g   backward_data: gradient g, filters X.
-// The gather kernels' LDS tiles carry large products at 2-3 times the fragments
-// fetched by each wave (512 x 2048 x 1000 in fp32: out 39 -> 28 us, dX 39 -> 29, dW
-// 44 -> 32); below 2.5e8 multiply-adds (64 x 3136 x 512: 12 us split over blocks)
-// they have too few tiles.
+// The gather kernels' LDS tiles carry large products at fewer fetches than the
+// fragments of each wave, but have fewer blocks (a long narrow product, 1000 x 4001 x
+// 101 in fp32: out 40 us, gathered 72; dW 26 and 32), so every edge is 256 or more,
+// and multiply-adds at least
+//   - fp32, dX and dW: 2.5e8 (512 x 2048 x 1000: dX 38 -> 32 us, dW 45 -> 38; 256 x
+//     1501 x 801: 41 -> 29, 18 -> 17.6; the LeNet layer 64 x 3136 x 512 has 1e8);
+//   - fp32 out, fp64 dX: 2e9 (1024 x 4096 x 1024: 162 -> 116 and 251 -> 171; 512 x
+//     2048 x 1000: 39 and 41, 57 and 61);
+//   - fp64 out and dW: never (at these sizes 207 and 208, 61 and 80; 204 and 269, 59
+//     and 71).
 ConvDims affine_dims(int N, int D, int M)
 {
     return ConvDims{1, D, 1, M, N, 1, 1, 1, 0, 1, M};
@@ -424,7 +430,8 @@ ConvDims affine_dims(int N, int D, int M)
 
 GatherPlan affine_gather(int dtype, int product, int N, int D, int M)
 {
-    if ((double)N * D * M < 2.5e8) return GatherPlan{};
+    if (std::min(N, std::min(D, M)) < 256 || (dtype == 0 && product != 1)) return GatherPlan{};
+    if ((double)N * D * M < (dtype == 1 && product != 0 ? 2.5e8 : 2e9)) return GatherPlan{};
     const ConvDims d = affine_dims(N, D, M);
     if (product == 1) return gather_wgrad_plan(dtype, d, 1);
     return gather_plan(dtype, product == 2, d, false);

@@ -68,12 +68,15 @@ def test_softmax_xent_wide_rows(nk, dt):
     assert_close(host(p), rp, dt, "probs")
 
 
-@pytest.mark.parametrize("dt", ["f64", "f32"])
-@pytest.mark.parametrize("shape", [(130, 2001, 1003), (520, 1024, 512)], ids=str)
-def test_large_affine_takes_the_gather_kernels(shape, dt):
+@pytest.mark.parametrize("dt,shape,taken", [
+    ("f32", (256, 2001, 1003), ("dX", "dW")), ("f32", (520, 1024, 512), ("dX", "dW")),
+    ("f32", (1030, 1950, 1001), ("forward", "dX", "dW")), ("f64", (1030, 1950, 1001), ("dX",)),
+    ("f32", (255, 2001, 1003), ()), ("f64", (520, 1024, 512), ())], ids=str)
+def test_large_affine_takes_the_gather_kernels(dt, shape, taken):
     N, D, M = shape
     tdt = torch.float64 if dt == "f64" else torch.float32
-    assert all(dmlnn.affine_plan(tdt, p, N, D, M, 0)["tile"] == 0 for p in ("forward", "dX", "dW"))
+    assert taken == tuple(p for p in ("forward", "dX", "dW")
+                          if dmlnn.affine_plan(tdt, p, N, D, M, 0)["tile"] == 0)
     print(f"\n[gpu] affine {shape} {dt}", flush=True)
     g = rng(54)
     X = rounded(np.maximum(g.standard_normal((N, D)), 0.0), dt)

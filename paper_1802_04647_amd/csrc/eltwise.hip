@@ -30,8 +30,8 @@ __global__ __launch_bounds__(256) void bias_add_relu_kernel(const T *X, const T 
 }
 
 // The same for totals under 2^31, V elements of a plane a thread at a time (one plane
-// is hw = HW / V of them): no 64-bit division per element, 16-byte accesses where
-// the planes and pointers allow them.  32 x 64 planes of 112x112 in fp32: 54 -> 35 us (205 MB).
+// is hw = HW / V of them): no 64-bit division per element, in fp32 16-byte accesses
+// where the planes and pointers allow them.  32 x 64 planes of 112x112 in fp32: 54 -> 35 us (205 MB).
 template <typename T, int V>
 __global__ __launch_bounds__(256) void bias_add_relu_vec_kernel(const T *X, const T *b, T *out,
                                                                 int total, FastDiv hw, FastDiv C,
@@ -53,7 +53,9 @@ template <typename T>
 hipError_t bias_vec(const T *X, const T *b, T *out, long long total, int C, int HW, int relu,
                     hipStream_t s)
 {
-    constexpr int V = 16 / (int)sizeof(T);
+    // fp64 stays at one element: 256 x 64 planes of 56x56 (823 MB) 141 us, with 16-byte
+    // accesses 164, by the 64-bit element walk 151.
+    constexpr int V = sizeof(T) == 4 ? 4 : 1;
     const bool vec = HW % V == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)out % 16 == 0;
     const int n = (int)(vec ? total / V : total);
     auto k = vec ? bias_add_relu_vec_kernel<T, V> : bias_add_relu_vec_kernel<T, 1>;
